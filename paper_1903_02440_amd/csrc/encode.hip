@@ -1312,6 +1312,7 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
     // few images (online steps): more, thinner bands, so that more workgroups share them
     while ((int64_t)B * nb < 128 && nb < H) nb = std::min(H, 2 * nb);
     R = (H + nb - 1) / nb;
+    nb = (H + R - 1) / R;  // the kernel's own count: bands of R whole rows may be fewer than asked for
     hipLaunchKernelGGL(k_filter, dim3((unsigned)(B * nb)), dim3(256), filter_lds(R), st, image, B, H, W, filters, C,
                        KF, filter_threshold, R, I);
     if (!t_first && !wave) return spk::check_launch("spk_encode_latency");

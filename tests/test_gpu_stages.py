@@ -529,6 +529,21 @@ def test_encode_parity(case):
     assert_equal(host(wave), rwave, "wave")
 
 
+@pytest.mark.parametrize("B,H,W", [(2, 160, 250), (2, 156, 286), (3, 100, 120)])
+def test_encode_few_images_stay_in_their_buffers(B, H, W):
+    # few images: the filter's bands are cut thinner than LDS asks for, and a height that they
+    # do not divide must not leave workgroups for images past the batch
+    g = synth.rng(460, H)
+    img, bank = synth.pink_noise_images(g, B, H, W), synth.gabor_bank()
+    room = torch.full((3 * B, 4, H, W), -7.0, dtype=torch.float32, device="cuda")
+    _, tf, inten = spk.spk_encode_latency(dev(img), dev(bank), 15, wave=False, intensities=room[:B])
+    sync()
+    I, rtf, _ = orc.encode(img, bank, 15, 0.0)
+    assert_equal(host(inten), I, "intensities")
+    assert_equal(host(tf), rtf, "t_first")
+    assert (host(room[B:]) == -7.0).all(), "intensities past the batch were written"
+
+
 @pytest.mark.parametrize("r,shape", [(0, (3, 6, 28, 28)), (2, (3, 6, 28, 28)), (8, (3, 6, 28, 28)),
                                      (30, (3, 6, 28, 28)), (8, (1, 2, 100, 250)), (3, (2, 1, 37, 5))])
 def test_local_normalization_parity(r, shape):
