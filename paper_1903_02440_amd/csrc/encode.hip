@@ -8,21 +8,22 @@
 // image fits in LDS (the MNIST-sized and other small inputs), is one kernel,
 // k_encode_small (one workgroup per image): filter, rank-order bins by radix
 // select, t_first and wave, with the intensity map never leaving LDS (it is
-// written out only when the caller asks for it).  Otherwise three kernels:
-//   1. k_filter: same-size cross-correlation of each u8 image with the C
-//      filters (double accumulation over the non-zero taps, one rounding to
-//      float, then values below the threshold set to 0).  One workgroup per
-//      (image, band of rows: the whole image when it fits) stages the
-//      zero-padded band in LDS and computes all channels.
-//   2. rank-order bins: k_encode_small without its filter step when the map
-//      has <= SMALL_MAX entries; else k_rank_select, one workgroup per image
-//      finding the T-1 bin boundaries by an MSD radix select (8 passes of 8
-//      bits) on the unique 64-bit keys  (float bits of I) << 32 | ~index  of
-//      the positive intensities, all boundaries sharing each pass's digit
-//      histograms, and
-//   3. k_expand_latency: every entry counts the boundaries its key does not
-//      exceed -- that count is its bin floor(rho*T/n) -- and writes t_first
-//      and the T planes of the wave (4 entries per thread, u32 stores).
+// written out only when the caller asks for it).  Larger maps take many
+// workgroups per image in every step:
+//   1. k_enc_prepare analyses the bank once and clears the digit histograms;
+//   2. k_filter_tile: same-size cross-correlation of each u8 image with the C
+//      filters (exact integer sums, or double accumulation over the non-zero
+//      taps, one rounding to float, then values below the threshold set to 0),
+//      one workgroup per (image, tile), counting the first digit of the
+//      positive intensities on the way (k_filter, one workgroup per band of
+//      rows, for banks of more than MAX_DERIV_C channels);
+//   3. k_rank_select .. k_rank_resolve: the T-1 bin boundaries, the keys
+//      (float bits of I) << 32 | ~index  at the ranks ceil((j+1) n / T), by a
+//      13-bit first digit per image and then, per digit that holds a boundary,
+//      the few entries with that digit only;
+//   4. k_expand_latency: every entry's bin floor(rho*T/n) is the number of
+//      boundaries its key does not exceed; t_first and the T planes of the
+//      wave are written 16 entries per thread.
 #include <algorithm>
 
 #include "common.hpp"
@@ -30,9 +31,6 @@
 namespace {
 
 constexpr int MAX_KF = 31;
-constexpr int SEL_THREADS = 1024;
-constexpr int MAX_GROUPS = 32;   // bin boundaries resolved per select batch
-constexpr int LDS_KEYS = 12288;  // intensities cached in LDS when N fits
 constexpr int SMALL_MAX = 8192;  // entries per image coded by one k_encode_small workgroup
 constexpr size_t SMALL_LDS = 60 * 1024;  // its dynamic LDS at most
 
@@ -172,184 +170,436 @@ __global__ __launch_bounds__(256) void k_filter(const uint8_t *__restrict__ img,
     }
 }
 
-// ------------------------------------------------------------------ rank select
+// ------------------------------------------------------------------ rank select (large maps)
+// What bounds it is latency, not bytes: an intensity map is read three times
+// (once while it is made), 4 bytes an entry.  One workgroup per image running
+// 8 digit passes over the whole map (the form before) took 1260 us for 64
+// images of 160,000 entries and 3090 us for 7 of 464,166, on 64 and 7 of the
+// 256 CUs.  Here every pass over the map uses all CUs and only the entries
+// that share their first digit with a boundary are looked at again: select,
+// collect and resolve take 36 and 22 us there, the histogram's pass none (the
+// filter counts).
 __device__ __forceinline__ uint64_t make_key(float v, uint32_t idx) {
     return ((uint64_t)__float_as_uint(v) << 32) | (uint64_t)(0xFFFFFFFFu - idx);
 }
 
-// Output per image: bounds[b][j] (j = 0..T-2) = key at rank ceil((j+1)*n/T)
-// in descending order, 0 when that rank is >= n; count[b] = n.
-__global__ __launch_bounds__(SEL_THREADS) void k_rank_select(const float *__restrict__ inten, int64_t N, int T,
-                                                             uint64_t *__restrict__ bounds,
-                                                             uint32_t *__restrict__ count) {
-    __shared__ uint32_t hist[MAX_GROUPS][256];
-    __shared__ uint64_t gprefix[MAX_GROUPS];
-    __shared__ uint64_t tprefix[MAX_GROUPS];
-    __shared__ uint32_t trank[MAX_GROUPS];
-    __shared__ int tgroup[MAX_GROUPS];
-    __shared__ int ngroups, ntarg;
-    __shared__ int red[SEL_THREADS / 64];
-    __shared__ float cache[LDS_KEYS];
+constexpr int RK_SHIFT = 18;          // first digit: float bits 30..18 (8 exponent, 5 mantissa bits)
+constexpr int RK_BINS = 1 << 13;
+constexpr int RK_T = 256;             // table rows per image (at most 254 boundaries)
+constexpr int RK_CHUNK = 4096;        // entries a workgroup takes at a time (16 per thread)
+constexpr int RK_LDS = 4096;          // keys of one digit resolved in LDS
+constexpr int RK_SUB = 1024;          // ... and of its second digits that hold boundaries
+constexpr int RK_GROUPS = 32;         // boundaries resolved at once by the digit passes
+constexpr int RK_HIST_MAX = 60 * 1024;  // entries a workgroup counts at most (16-bit counters)
 
-    const int b = blockIdx.x;
-    const float *I = inten + (int64_t)b * N;
-    const bool cached = N <= LDS_KEYS;
-    const int tid = threadIdx.x;
+// Per-call workspace of the large-map rank code.
+struct RankWork {
+    uint32_t *hist;    // [B][RK_BINS] entries per first digit
+    uint8_t *gmap;     // [B][RK_BINS] number of the digit among those with boundaries (0xFF: none)
+    uint32_t *cursor;  // [B][RK_T] next free list entry of each such digit
+    int4 *targ;        // [B][RK_T] per boundary: its digit's list start and length, its rank there, and
+                       // the number of boundaries in the digit (at the digit's first boundary, else 0)
+    uint64_t *list;    // [B][N] keys of the entries whose digit holds a boundary, digit by digit
+    uint64_t *bounds;  // [B][T-1] the boundaries' keys, descending; 0 where the rank is past the last entry
+};
 
-    int cnt = 0;
-    for (int64_t i = tid; i < N; i += SEL_THREADS) {
-        const float v = I[i];
-        if (cached) cache[i] = v;
-        cnt += v > 0.0f;
+// First digits counted in LDS as 16-bit halves, RK_BINS / 2 words.
+__device__ __forceinline__ void digit_count(uint32_t *h, float v) {
+    if (v > 0.0f) {
+        const uint32_t d = __float_as_uint(v) >> RK_SHIFT;
+        atomicAdd(&h[d >> 1], 1u << (16 * (d & 1)));
     }
-    cnt = spk::wave_sum_i32(cnt);
-    if ((tid & 63) == 0) red[tid >> 6] = cnt;
-    __syncthreads();
-    uint32_t n = 0;
-    for (int w = 0; w < SEL_THREADS / 64; ++w) n += (uint32_t)red[w];
-    if (tid == 0) count[b] = n;
+}
+__device__ __forceinline__ void digit_merge(const uint32_t *h, uint32_t *__restrict__ hist) {
+    for (int i = threadIdx.x; i < RK_BINS / 2; i += 256) {
+        const uint32_t w = h[i];
+        if (w & 0xFFFFu) atomicAdd(&hist[2 * i], w & 0xFFFFu);
+        if (w >> 16) atomicAdd(&hist[2 * i + 1], w >> 16);
+    }
+}
 
-    for (int j0 = 0; j0 < T - 1; j0 += MAX_GROUPS) {
-        const int jn = min(MAX_GROUPS, T - 1 - j0);
-        if (tid < jn) {
-            const uint64_t r = ((uint64_t)(j0 + tid + 1) * n + T - 1) / T;  // ceil((j+1) n / T)
-            trank[tid] = (uint32_t)r;
-            tprefix[tid] = 0;
-            bounds[(int64_t)b * (T - 1) + j0 + tid] = 0;
+// First-digit histogram of given intensities.  Grid (image, chunk of `per` entries).
+__global__ __launch_bounds__(256) void k_rank_hist(const float *__restrict__ inten, int64_t N, int chunks, int per,
+                                                   uint32_t *__restrict__ hist) {
+    __shared__ uint32_t h[RK_BINS / 2];
+    const int b = blockIdx.x / chunks, ch = blockIdx.x % chunks;
+    const float *I = inten + (int64_t)b * N;
+    for (int i = threadIdx.x; i < RK_BINS / 2; i += 256) h[i] = 0;
+    __syncthreads();
+    const int64_t e0 = (int64_t)ch * per, e1 = min<int64_t>(N, e0 + per);
+    for (int64_t i0 = e0 + threadIdx.x; i0 < e1; i0 += 8 * 256) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = I[min<int64_t>(i0 + k * 256, e1 - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (i0 + k * 256 < e1) digit_count(h, v[k]);
+    }
+    __syncthreads();
+    digit_merge(h, hist + (int64_t)b * RK_BINS);
+}
+
+// One workgroup per image: the suffix sums of the first digits, the digit and
+// the rank inside it of every boundary, and the list segments of the digits
+// that hold boundaries.
+__global__ __launch_bounds__(1024) void k_rank_select(int T, RankWork w) {
+    __shared__ uint32_t S[RK_BINS + 1];  // entries with digit >= d
+    __shared__ uint32_t wsum[16], gsum[4];
+    __shared__ int gcnt[4];
+    __shared__ int tb[RK_T];             // each boundary's digit, -1: none
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nb = T - 1;
+    const uint4 *h4 = reinterpret_cast<const uint4 *>(w.hist + (int64_t)b * RK_BINS) + 2 * tid;
+    const uint4 ha = h4[0], hb = h4[1];
+    const uint32_t h[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
+    uint32_t loc = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) loc += h[q];
+    const uint32_t pre = wave_prefix_sum(loc), tot = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63);
+    if (lane == 0) wsum[wv] = tot;
+    reinterpret_cast<uint2 *>(w.gmap + (int64_t)b * RK_BINS)[tid] = uint2{0xFFFFFFFFu, 0xFFFFFFFFu};
+    __syncthreads();
+    uint32_t above = tot - pre;
+    for (int q = wv + 1; q < 16; ++q) above += wsum[q];
+#pragma unroll
+    for (int q = 7; q >= 0; --q) {
+        above += h[q];
+        S[8 * tid + q] = above;
+    }
+    if (tid == 0) S[RK_BINS] = 0;
+    __syncthreads();
+    const uint32_t n = S[0];
+    int d = -1;
+    uint32_t cnt = 0, rr = 0;
+    if (tid < nb) {
+        const uint32_t r = (uint32_t)(((uint64_t)(tid + 1) * n + T - 1) / T);  // ceil((j+1) n / T)
+        if (r < n) {
+            int lo = 0, hi = RK_BINS - 1;  // the largest digit with S[d] > r
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (S[mid] > r) lo = mid;
+                else hi = mid - 1;
+            }
+            d = lo;
+            cnt = S[d] - S[d + 1];
+            rr = r - S[d + 1];
+        } else {
+            w.bounds[(int64_t)b * nb + tid] = 0;
+        }
+    }
+    if (tid < RK_T) tb[tid] = d;
+    __syncthreads();
+    const bool lead = d >= 0 && (tid == 0 || tb[tid - 1] != d);
+    const uint64_t lm = __ballot(lead);
+    const uint32_t gp = wave_prefix_sum(lead ? cnt : 0u);
+    if (tid < RK_T && lane == 63) {
+        gsum[wv] = gp;
+        gcnt[wv] = __popcll(lm);
+    }
+    __syncthreads();
+    if (tid < nb) {
+        uint32_t start = gp - (lead ? cnt : 0u);
+        int g = __popcll(lm & ((1ull << lane) - 1ull));
+        for (int q = 0; q < wv; ++q) {
+            start += gsum[q];
+            g += gcnt[q];
+        }
+        int nt = 0;
+        if (lead) {
+            nt = 1;
+            while (tid + nt < nb && tb[tid + nt] == d) ++nt;
+            w.gmap[(int64_t)b * RK_BINS + d] = (uint8_t)g;
+            w.cursor[(int64_t)b * RK_T + g] = start;
+        }
+        w.targ[(int64_t)b * RK_T + tid] = int4{(int)start, (int)cnt, (int)rr, nt};
+    }
+}
+
+// The keys of the entries whose first digit holds a boundary, into the digits'
+// list segments (in no particular order within one).  Grid (image, chunk): a
+// workgroup numbers its entries per digit in LDS and reserves their places with
+// one global addition per digit and RK_CHUNK entries.
+__global__ __launch_bounds__(256) void k_rank_collect(const float *__restrict__ inten, int64_t N, int chunks,
+                                                      RankWork w) {
+    __shared__ uint4 gm4[RK_BINS / 16];
+    __shared__ uint32_t cnt[RK_T], base[RK_T];
+    const int b = blockIdx.x / chunks, ch = blockIdx.x % chunks, tid = threadIdx.x;
+    const float *I = inten + (int64_t)b * N;
+    for (int i = tid; i < RK_BINS / 16; i += 256)
+        gm4[i] = reinterpret_cast<const uint4 *>(w.gmap + (int64_t)b * RK_BINS)[i];
+    const uint8_t *gm = reinterpret_cast<const uint8_t *>(gm4);
+    for (int64_t c0 = (int64_t)ch * RK_CHUNK; c0 < N; c0 += (int64_t)chunks * RK_CHUNK) {
+        cnt[tid] = 0;
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = I[min<int64_t>(c0 + k * 256 + tid, N - 1)];
+        __syncthreads();
+        uint32_t at[16];  // group << 16 | place among the workgroup's entries of the group
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            at[k] = 0xFFFFFFFFu;
+            if (v[k] > 0.0f && c0 + k * 256 + tid < N) {
+                const uint32_t g = gm[__float_as_uint(v[k]) >> RK_SHIFT];
+                if (g != 0xFFu) at[k] = g << 16 | atomicAdd(&cnt[g], 1u);
+            }
         }
         __syncthreads();
-        if (tid == 0) {
-            int m = 0;
-            for (int j = 0; j < jn; ++j) m += trank[j] < n;
-            ntarg = m;  // active targets are a prefix (ranks grow with j)
+        if (cnt[tid]) base[tid] = atomicAdd(&w.cursor[(int64_t)b * RK_T + tid], cnt[tid]);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (at[k] != 0xFFFFFFFFu)
+                w.list[(int64_t)b * N + base[at[k] >> 16] + (at[k] & 0xFFFFu)] =
+                    make_key(v[k], (uint32_t)(c0 + k * 256 + tid));
+    }
+}
+
+// Grid (boundary, image): the workgroup of a digit's first boundary finds the
+// keys of all boundaries in that digit.  Segments of at most RK_LDS keys go
+// into LDS: a second digit (the next 10 float bits) by histogram, then the
+// entries with the boundaries' second digits, at most RK_SUB of them, ranked
+// directly (the number of larger keys).  Longer segments, or many equal
+// values, take an MSD radix select over the rest of the key, 8 bits a pass.
+__global__ __launch_bounds__(256) void k_rank_resolve(int64_t N, int T, RankWork w) {
+    __shared__ uint64_t lk[RK_LDS];      // keys; the digit passes' histograms [RK_GROUPS][256]
+    __shared__ uint64_t sub[RK_SUB];     // keys with the boundaries' second digits; the passes' prefixes
+    __shared__ uint32_t hist[1025];      // second digits: entries with digit >= d
+    __shared__ uint32_t mark[32], trank[RK_T], wsum[4];
+    __shared__ int tsub[RK_T], s_m, s_ng;
+    const int j0 = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int4 *tg = w.targ + (int64_t)b * RK_T + j0;
+    const int4 t0 = tg[0];
+    const int nt = t0.w, cnt = t0.y;
+    if (nt == 0) return;  // (uniform)
+    const uint64_t *L = w.list + (int64_t)b * N + t0.x;
+    uint64_t *bounds = w.bounds + (int64_t)b * (T - 1) + j0;
+    if (cnt <= RK_LDS) {
+        for (int i0 = tid; i0 < cnt; i0 += 4 * 256) {
+            uint64_t v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = L[min(i0 + k * 256, cnt - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i0 + k * 256 < cnt) lk[i0 + k * 256] = v[k];
+        }
+        for (int i = tid; i < 1024; i += 256) hist[i] = 0;
+        if (tid < 32) mark[tid] = 0;
+        if (tid == 0) s_m = 0;
+        __syncthreads();
+        for (int i = tid; i < cnt; i += 256) atomicAdd(&hist[(uint32_t)(lk[i] >> 40) & 1023u], 1u);
+        __syncthreads();
+        uint32_t h[4], loc = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            h[q] = hist[4 * tid + q];
+            loc += h[q];
+        }
+        const uint32_t pre = wave_prefix_sum(loc), tot = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63);
+        if (lane == 0) wsum[wv] = tot;
+        __syncthreads();
+        uint32_t above = tot - pre;
+        for (int q = wv + 1; q < 4; ++q) above += wsum[q];
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+            above += h[q];
+            hist[4 * tid + q] = above;
+        }
+        if (tid == 0) hist[1024] = 0;
+        __syncthreads();
+        if (tid < nt) {
+            const uint32_t r = (uint32_t)tg[tid].z;
+            int lo = 0, hi = 1023;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (hist[mid] > r) lo = mid;
+                else hi = mid - 1;
+            }
+            tsub[tid] = lo;
+            trank[tid] = r - hist[lo + 1];
+            atomicOr(&mark[lo >> 5], 1u << (lo & 31));
         }
         __syncthreads();
-        const int m = ntarg;
-        if (m == 0) continue;
-        for (int pass = 0; pass < 8; ++pass) {
-            const int shift = 56 - 8 * pass;
-            // group the active targets by their current prefix (non-increasing in j)
-            if (tid == 0) {
+        for (int i = tid; i < cnt; i += 256) {
+            const uint64_t key = lk[i];
+            const uint32_t d = (uint32_t)(key >> 40) & 1023u;
+            if ((mark[d >> 5] >> (d & 31)) & 1u) {
+                const int at = atomicAdd(&s_m, 1);
+                if (at < RK_SUB) sub[at] = key;
+            }
+        }
+        __syncthreads();
+        const int m = s_m;
+        if (m <= RK_SUB) {
+            for (int i = tid; i < m; i += 256) {
+                const uint64_t key = sub[i], d = key >> 40;
+                uint32_t rho = 0;
+                for (int u = 0; u < m; ++u) {
+                    const uint64_t o = sub[u];
+                    rho += o > key && (o >> 40) == d;
+                }
+                for (int j = 0; j < nt; ++j)
+                    if (tsub[j] == (int)((uint32_t)d & 1023u) && trank[j] == rho) bounds[j] = key;
+            }
+            return;
+        }
+        __syncthreads();  // lk is reused below
+    }
+    // 8-bit digits 48..0; the top 8 key bits are the same for the whole segment
+    uint32_t(*gh)[256] = reinterpret_cast<uint32_t(*)[256]>(lk);
+    uint64_t *gpre = sub, *tpre = sub + RK_GROUPS;
+    int *tgrp = tsub;
+    for (int q0 = 0; q0 < nt; q0 += RK_GROUPS) {
+        const int m = min(RK_GROUPS, nt - q0);
+        if (tid < m) {
+            trank[tid] = (uint32_t)tg[q0 + tid].z;
+            tpre[tid] = L[0] >> 56;
+        }
+        __syncthreads();
+        for (int shift = 48; shift >= 0; shift -= 8) {
+            if (tid == 0) {  // the distinct prefixes (non-increasing in j)
                 int g = -1;
                 for (int j = 0; j < m; ++j) {
-                    if (g < 0 || tprefix[j] != gprefix[g]) gprefix[++g] = tprefix[j];
-                    tgroup[j] = g;
+                    if (g < 0 || tpre[j] != gpre[g]) gpre[++g] = tpre[j];
+                    tgrp[j] = g;
                 }
-                ngroups = g + 1;
+                s_ng = g + 1;
             }
             __syncthreads();
-            const int ng = ngroups;
-            for (int i = tid; i < ng * 256; i += SEL_THREADS) (&hist[0][0])[i] = 0;
+            const int ng = s_ng;
+            for (int i = tid; i < ng * 256; i += 256) (&gh[0][0])[i] = 0;
             __syncthreads();
-            for (int64_t i = tid; i < N; i += SEL_THREADS) {
-                const float v = cached ? cache[i] : I[i];
-                if (!(v > 0.0f)) continue;
-                const uint64_t key = make_key(v, (uint32_t)i);
-                const uint64_t pre = pass == 0 ? 0 : (key >> (shift + 8));
-                // binary search among the group prefixes (sorted descending)
-                int lo = 0, hi = ng - 1, g = -1;
-                while (lo <= hi) {
-                    const int mid = (lo + hi) >> 1;
-                    const uint64_t gp = gprefix[mid];
-                    if (gp == pre) { g = mid; break; }
-                    if (gp > pre) lo = mid + 1; else hi = mid - 1;
+            for (int i0 = tid; i0 < cnt; i0 += 4 * 256) {
+                uint64_t v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = L[min(i0 + k * 256, cnt - 1)];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (i0 + k * 256 >= cnt) break;
+                    const uint64_t pk = v[k] >> (shift + 8);
+                    int lo = 0, hi = ng - 1;  // gpre is descending
+                    while (lo <= hi) {
+                        const int mid = (lo + hi) >> 1;
+                        const uint64_t gp = gpre[mid];
+                        if (gp == pk) {
+                            atomicAdd(&gh[mid][(uint32_t)(v[k] >> shift) & 255u], 1u);
+                            break;
+                        }
+                        if (gp > pk) lo = mid + 1;
+                        else hi = mid - 1;
+                    }
                 }
-                if (g >= 0) atomicAdd(&hist[g][(key >> shift) & 255u], 1u);
             }
             __syncthreads();
-            // per group, suffix sums over the digits (digit 255 first): one wave per group
-            for (int g = tid >> 6; g < ng; g += SEL_THREADS / 64) {
-                const int lane = tid & 63;
+            for (int g = wv; g < ng; g += 4) {  // suffix sums over the digits: one wave per group
                 uint32_t h[4], loc = 0;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    h[q] = hist[g][4 * lane + q];
+                    h[q] = gh[g][4 * lane + q];
                     loc += h[q];
                 }
-                uint32_t suf = loc;  // sum over lanes >= lane
+                const uint32_t pre = wave_prefix_sum(loc);
+                uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63) - pre;
 #pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t o = __shfl_down(suf, d, 64);
-                    if (lane + d < 64) suf += o;
-                }
-                uint32_t above = suf - loc;  // digits held by higher lanes
                 for (int q = 3; q >= 0; --q) {
                     above += h[q];
-                    hist[g][4 * lane + q] = above;  // now: entries with digit >= 4*lane+q
+                    gh[g][4 * lane + q] = above;
                 }
             }
             __syncthreads();
             if (tid < m) {
-                // the digit d with S[d+1] <= r < S[d], where S[d] = entries with digit >= d
-                const int g = tgroup[tid];
+                const int g = tgrp[tid];
                 const uint32_t r = trank[tid];
-                int lo = 0, hi = 255;  // S[0] > r holds: the rank exists in this group
+                int lo = 0, hi = 255;  // gh[g][0] > r holds: the rank exists in this group
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
-                    if (hist[g][mid] > r) lo = mid; else hi = mid - 1;
+                    if (gh[g][mid] > r) lo = mid;
+                    else hi = mid - 1;
                 }
-                const int d = lo;
-                const uint32_t above = d < 255 ? hist[g][d + 1] : 0u;
-                trank[tid] = r - above;
-                tprefix[tid] = (tprefix[tid] << 8) | (uint64_t)d;
+                trank[tid] = r - (lo < 255 ? gh[g][lo + 1] : 0u);
+                tpre[tid] = (tpre[tid] << 8) | (uint64_t)lo;
             }
             __syncthreads();
         }
-        if (tid < m) bounds[(int64_t)b * (T - 1) + j0 + tid] = tprefix[tid];
+        if (tid < m) bounds[q0 + tid] = tpre[tid];
         __syncthreads();
     }
 }
 
-// t_first = number of boundaries K_j with key <= K_j (the K_j are non-increasing).
-__device__ __forceinline__ int bin_of(uint64_t key, const uint64_t *kb, int nb) {
-    int lo = 0, hi = nb;  // first j with kb[j] < key
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (kb[mid] >= key) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
+// Bytes of any alignment, as one wide access where the hardware allows it.
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t w[4];
+};
+struct __attribute__((packed, aligned(4))) Float4u {
+    float v[4];
+};
 
+// t_first of an entry = the number of boundaries K_j with key <= K_j (the K_j
+// are non-increasing), by a fixed-step search over the boundaries padded with
+// zeros to a power of two.  A thread codes 16 consecutive entries of one image
+// and writes each plane's 16 bytes at once, whatever the plane's alignment:
+// bound by these writes (T + 1 bytes an entry).  4 bytes a store before, and
+// single bytes where the entries per image are no multiple of 4: 64 images of
+// 160,000 entries, T = 30, 69 -> 58 us (5.7 TB/s); 7 of 464,166, T = 20, 56 -> 19 us.
 __global__ __launch_bounds__(256) void k_expand_latency(const float *__restrict__ inten, int64_t N, int T,
                                                         const uint64_t *__restrict__ bounds,
                                                         uint8_t *__restrict__ tf_out, uint8_t *__restrict__ wave,
                                                         int chunks) {
     __shared__ uint64_t kb[256];
-    const int b = blockIdx.x / chunks, ch = blockIdx.x % chunks;
-    const int nbnd = T - 1;
-    for (int j = threadIdx.x; j < nbnd; j += blockDim.x) kb[j] = bounds[(int64_t)b * nbnd + j];
-    __syncthreads();
+    const int b = blockIdx.x / chunks, ch = blockIdx.x % chunks, nb = T - 1;
+    kb[threadIdx.x] = (int)threadIdx.x < nb ? bounds[(int64_t)b * nb + threadIdx.x] : 0;
+    int nbp = 1;
+    while (nbp <= nb) nbp <<= 1;
     const float *I = inten + (int64_t)b * N;
-    const bool vec = (N % 4) == 0;
-    const int64_t groups = (N + 3) / 4;
-    for (int64_t q = (int64_t)ch * blockDim.x + threadIdx.x; q < groups; q += (int64_t)chunks * blockDim.x) {
-        uint32_t tv = 0;
-        int t4[4];
+    uint8_t *tf = tf_out ? tf_out + (int64_t)b * N : nullptr;
+    uint8_t *wv = wave ? wave + (int64_t)b * T * N : nullptr;
+    __syncthreads();
+    const int64_t groups = (N + 15) / 16;
+    for (int64_t q = (int64_t)ch * 256 + threadIdx.x; q < groups; q += (int64_t)chunks * 256) {
+        const int64_t i0 = 16 * q;
+        const int n = (int)min<int64_t>(16, N - i0);
+        float v[16];
+        if (n == 16) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t i = q * 4 + j;
-            int t = T;
-            if (i < N) {
-                const float v = I[i];
-                if (v > 0.0f) t = bin_of(make_key(v, (uint32_t)i), kb, nbnd);
+            for (int k = 0; k < 4; ++k) {
+                const Float4u f = *reinterpret_cast<const Float4u *>(I + i0 + 4 * k);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[4 * k + j] = f.v[j];
             }
-            t4[j] = t;
-            tv |= (uint32_t)t << (8 * j);
-        }
-        if (vec) {
-            if (tf_out) *reinterpret_cast<uint32_t *>(tf_out + (int64_t)b * N + q * 4) = tv;
-            if (wave)
-                for (int t = 0; t < T; ++t)
-                    *reinterpret_cast<uint32_t *>(wave + ((int64_t)b * T + t) * N + q * 4) = spk::spikes4(tv, t, T);
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t i = q * 4 + j;
-                if (i >= N) break;
-                if (tf_out) tf_out[(int64_t)b * N + i] = (uint8_t)t4[j];
-                if (wave)
-                    for (int t = 0; t < T; ++t) wave[((int64_t)b * T + t) * N + i] = (uint8_t)(t >= t4[j]);
-            }
+            for (int k = 0; k < 16; ++k) v[k] = k < n ? I[i0 + k] : 0.0f;
+        }
+        Bytes16 t16;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int pos[4] = {0, 0, 0, 0};
+            uint64_t key[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) key[j] = make_key(v[4 * k + j], (uint32_t)(i0 + 4 * k + j));
+            for (int step = nbp >> 1; step > 0; step >>= 1)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) pos[j] += kb[pos[j] + step - 1] >= key[j] ? step : 0;
+            t16.w[k] = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t16.w[k] |= (uint32_t)(v[4 * k + j] > 0.0f ? pos[j] : T) << (8 * j);
+        }
+        if (n == 16) {
+            if (tf) *reinterpret_cast<Bytes16 *>(tf + i0) = t16;
+            if (wv)
+                for (int t = 0; t < T; ++t) {
+                    Bytes16 o;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) o.w[k] = spk::spikes4(t16.w[k], t, T);
+                    *reinterpret_cast<Bytes16 *>(wv + (int64_t)t * N + i0) = o;
+                }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                if (k < n) {
+                    const int t1 = (int)((t16.w[k >> 2] >> (8 * (k & 3))) & 255u);
+                    if (tf) tf[i0 + k] = (uint8_t)t1;
+                    if (wv)
+                        for (int t = 0; t < T; ++t) wv[(int64_t)t * N + i0 + k] = (uint8_t)(t >= t1);
+                }
         }
     }
 }
@@ -507,20 +757,16 @@ __device__ __forceinline__ void tap_row(const P *row, const T *tr, int wx, A &ac
     rest(wx - u0, row + u0, tr + u0, acc);
 }
 
-// 8 consecutive outputs of row y, columns 8*xg.., of computed channel slot k
-// (channel c, and the negated channel after it when that one is derived), the
-// threshold applied.  Returns the number of positive outputs.
+// The 8 sums of row y, columns 8*xg.., of computed channel slot k (channel c).
 //  * double form: sums in ky-then-kx order over the channel's box of taps,
-//    one rounding to float;
-//  * integer form: int32 sums of tap 2^s times pixel, exact, times 2^-s and
-//    rounded once to float -- the same value, every partial sum of the
-//    double form being exact for such taps.
+//    one rounding to float by the caller;
+//  * integer form: int32 sums of tap 2^s times pixel, exact, times 2^-s -- the
+//    same value, every partial sum of the double form being exact for such taps.
 template <bool INT>
-__device__ __forceinline__ int filter_item(const FiltCtx &fx, int k, int c, int xg, int y) {
+__device__ __forceinline__ void filter_sums(const FiltCtx &fx, int k, int c, int xg, int y, double (&val)[8]) {
     constexpr int CW = 8;
     const int ya = fx.bbox[4 * c], yb = fx.bbox[4 * c + 1], xa = fx.bbox[4 * c + 2], xb = fx.bbox[4 * c + 3];
     const int wx = xb - xa + 1;
-    double val[CW];
     if constexpr (INT) {
         int acc[CW];
 #pragma unroll
@@ -568,6 +814,16 @@ __device__ __forceinline__ int filter_item(const FiltCtx &fx, int k, int c, int 
                     });
         }
     }
+}
+
+// The item's outputs of a small map, the threshold applied, and those of the
+// negated channel after it when that one is derived, into the LDS map.
+// Returns the number of positive outputs.
+template <bool INT>
+__device__ __forceinline__ int filter_item(const FiltCtx &fx, int k, int c, int xg, int y) {
+    constexpr int CW = 8;
+    double val[CW];
+    filter_sums<INT>(fx, k, c, xg, y, val);
     const bool dn = c + 1 < fx.C && fx.deriv[c + 1];
     const int HW = fx.H * fx.W;
     int npos = 0;
@@ -590,6 +846,159 @@ __device__ __forceinline__ int filter_item(const FiltCtx &fx, int k, int c, int 
         }
     }
     return npos;
+}
+
+// The analysis of a filter bank by one workgroup of ENC_THREADS threads (the
+// bank's floats staged in L.ft): which channels are computed, in which order,
+// their tap boxes, and the taps of the integer or the double form.
+struct BankLds {
+    float *ft;        // C * KF * KF taps as given (the double form's taps replace them)
+    uint32_t *itaps;  // integer form: packed tap pairs
+    double *dtaps;    // double form: the computed channels' boxes (the memory of ft)
+    int *bbox, *deriv, *order, *toff, *tstr;
+    uint32_t *s_ex;   // MAX_DERIV_C words of LDS
+    int *ncomp, *sexp;  // computed channels; the integer form's s, or -1 for the double form
+};
+__device__ __forceinline__ void analyse_bank(const float *__restrict__ filt, int C, int KF, const BankLds &L) {
+    float *ft = L.ft;
+    int *bbox = L.bbox, *deriv = L.deriv, *order = L.order, *toff = L.toff, *tstr = L.tstr;
+    uint32_t *s_ex = L.s_ex;
+    int &s_ncomp = *L.ncomp, &s_s = *L.sexp;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, KK = KF * KF;
+    const bool order_c = C <= MAX_DERIV_C;  // negated channels, cost order and integer form only then
+    __syncthreads();
+    // per channel (one wave each): bounding box of the non-zero taps, whether the
+    // taps are the exact negation of the previous channel's, and the integer
+    // form's statistics (fraction bits and largest binary exponent of the taps)
+    for (int c = wid; c < C; c += ENC_THREADS / 64) {
+        int ya = KF, yb = -1, xa = KF, xb = -1, fb = 0, em = -400;
+        bool neg = c > 0 && order_c;
+        for (int i = lane; i < KK; i += 64) {
+            const float f = ft[c * KK + i];
+            if (f != 0.0f) {
+                const int ky = i / KF, kx = i - ky * KF;
+                ya = min(ya, ky); yb = max(yb, ky); xa = min(xa, kx); xb = max(xb, kx);
+                const uint32_t u = __float_as_uint(f), e = (u >> 23) & 255u, m = u & 0x7FFFFFu;
+                if (e == 255u) {
+                    fb = 4095;  // not finite: the double form
+                } else {
+                    const uint32_t mm = e ? (m | 0x800000u) : m;
+                    const int e0 = (int)(e ? e : 1u) - 150;  // value = mm * 2^e0
+                    fb = max(fb, -(e0 + (int)__builtin_ctz(mm)));
+                    em = max(em, e0 + 31 - (int)__builtin_clz(mm));
+                }
+            }
+            if (c > 0) neg = neg && (f == -ft[(c - 1) * KK + i]);
+        }
+        // three reductions of 16-bit pairs: (ya, xa) by min, (yb + 1, xb + 1) and
+        // (fraction bits, exponent + 512) by max
+        const uint32_t lo = wave_min_u16x2((uint32_t)ya | ((uint32_t)xa << 16));
+        const uint32_t hi = wave_max_u16x2((uint32_t)(yb + 1) | ((uint32_t)(xb + 1) << 16));
+        const uint32_t ex = wave_max_u16x2((uint32_t)max(fb, 0) | ((uint32_t)(em + 512) << 16));
+        const bool all_neg = __ballot(!neg) == 0;
+        if (lane == 0) {
+            bbox[4 * c] = (int)(lo & 0xFFFFu); bbox[4 * c + 1] = (int)(hi & 0xFFFFu) - 1;
+            bbox[4 * c + 2] = (int)(lo >> 16); bbox[4 * c + 3] = (int)(hi >> 16) - 1;
+            deriv[c] = all_neg ? 1 : 0;
+            if (order_c) s_ex[c] = ex;
+        }
+    }
+    __syncthreads();
+    if (wid == 0) {
+        if (order_c) {  // lane c: channel c
+            // A negated channel is derived only from a computed one: in a run of
+            // channels that each negate the one before, following a channel that
+            // does not, every second one is derived.
+            const bool neg = lane < C && deriv[lane] != 0;
+            const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1;
+            const int c0 = 63 - __clzll(~__ballot(neg) & upto);  // channel 0 never negates
+            const bool der = neg && ((lane - c0) & 1);
+            const bool comp = lane < C && !der;
+            // computed channels in decreasing order of tap area, equal areas by index
+            const int area = comp ? tap_area(bbox, lane) : -1;
+            // the integer form: every computed tap a multiple of 2^-s, |tap| 2^s <
+            // 2^15, and KK * 255 * 2^(exponent + s + 1) < 2^31 bounds every sum
+            const uint32_t ex = comp ? s_ex[lane] : 0u;
+            const uint32_t exm = wave_max_u16x2(comp ? ex : (uint32_t)(112u << 16));  // (-400 + 512) << 16
+            const int sfb = (int)(exm & 0xFFFFu), sem = (int)(exm >> 16) - 512;
+            const bool exact = sfb <= 126 && sem + sfb <= 14 &&
+                               (sem + sfb + 1 < 0 || ((int64_t)KK * 255 << (sem + sfb + 1)) < (1LL << 31));
+            const int wy = comp ? bbox[4 * lane + 1] - bbox[4 * lane] + 1 : 0;
+            const int wxl = comp ? bbox[4 * lane + 3] - bbox[4 * lane + 2] + 1 : 0;
+            const int size = area <= 0 ? 0 : exact ? ((wy + 1) >> 1) * wxl : area;
+            int rank = 0, off = 0;
+            for (int k = 0; k < C; ++k) {
+                const int ak = __builtin_amdgcn_readlane(area, k), sk = __builtin_amdgcn_readlane(size, k);
+                const bool before = ak > area || (ak == area && k < lane);
+                rank += before;
+                off += before && ak >= 0 ? sk : 0;
+            }
+            if (lane < C) {
+                deriv[lane] = der ? 1 : 0;
+                if (comp) {
+                    order[rank] = lane;
+                    toff[rank] = off;
+                    tstr[rank] = wxl;
+                }
+            }
+            const int nc = __popcll(__ballot(comp));
+            if (lane == 0) {
+                s_ncomp = nc;
+                s_s = exact ? sfb : -1;
+            }
+            if (exact) {
+                // this wave packs the integer form's taps (int16 pairs of tap rows ky,
+                // ky + 1; zero past the box), slot after slot, while the others wait
+                uint32_t *itp = L.itaps;
+                const int bya = comp ? bbox[4 * lane] : 0, byb = comp ? bbox[4 * lane + 1] : 0;
+                const int bxa = comp ? bbox[4 * lane + 2] : 0;
+                for (int k = 0; k < nc; ++k) {
+                    const int c = (int)__builtin_ctzll(__ballot(comp && rank == k));  // slot k's channel
+                    const int ya = __builtin_amdgcn_readlane(bya, c), yb = __builtin_amdgcn_readlane(byb, c);
+                    const int xa = __builtin_amdgcn_readlane(bxa, c), wk = __builtin_amdgcn_readlane(wxl, c);
+                    const int n = ((yb - ya + 2) >> 1) * wk;
+                    uint32_t *tp = itp + __builtin_amdgcn_readlane(off, c);
+                    for (int e = lane; e < n; e += 64) {
+                        const int kp = e / wk, u = e - kp * wk, ky = ya + 2 * kp;
+                        const int q0 = (int)ldexpf(ft[c * KK + ky * KF + xa + u], sfb);
+                        const int q1 = ky + 1 <= yb ? (int)ldexpf(ft[c * KK + (ky + 1) * KF + xa + u], sfb) : 0;
+                        tp[e] = ((uint32_t)q0 & 0xFFFFu) | ((uint32_t)q1 << 16);
+                    }
+                }
+            }
+        } else {  // every channel computed, in index order, double form with full rows
+            for (int c = lane; c < C; c += 64) {
+                order[c] = c;
+                toff[c] = c * KK + max(bbox[4 * c], 0) * KF + max(bbox[4 * c + 2], 0);
+                tstr[c] = KF;
+            }
+            if (lane == 0) {
+                s_ncomp = C;
+                s_s = -1;
+            }
+        }
+    }
+    __syncthreads();
+    const int ncomp = s_ncomp;
+    if (s_s < 0) {  // (the integer form's taps were packed with the order)
+        // per computed channel: its box of taps as doubles (whole rows when C is
+        // large), read from global memory since they replace the staged floats
+        double *tp = L.dtaps;
+        for (int k = 0; k < ncomp; ++k) {
+            const int c = order[k];
+            if (order_c) {
+                const int ya = bbox[4 * c], xa = bbox[4 * c + 2], wxl = tstr[k];
+                const int n = max(0, (bbox[4 * c + 1] - ya + 1)) * wxl;
+                for (int e = tid; e < n; e += ENC_THREADS) {
+                    const int r = e / wxl, u = e - r * wxl;
+                    tp[toff[k] + e] = (double)filt[c * KK + (ya + r) * KF + xa + u];
+                }
+            } else {
+                for (int e = tid; e < KK; e += ENC_THREADS) tp[c * KK + e] = (double)filt[c * KK + e];
+            }
+        }
+        __syncthreads();  // (uniform)
+    }
 }
 
 template <bool FILTER>
@@ -648,142 +1057,13 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void k_encode_small(const uint8_t *
                 asm volatile("" : "+v"(hi));  // keeps the shift here, out of the load's branch
                 pairs[i] = v.x | hi << 16;
             });
-        const bool order_c = C <= MAX_DERIV_C;  // negated channels, cost order and integer form only then
-        __syncthreads();
-        // per channel (one wave each): bounding box of the non-zero taps, whether the
-        // taps are the exact negation of the previous channel's, and the integer
-        // form's statistics (fraction bits and largest binary exponent of the taps)
-        for (int c = wid; c < C; c += ENC_THREADS / 64) {
-            int ya = KF, yb = -1, xa = KF, xb = -1, fb = 0, em = -400;
-            bool neg = c > 0 && order_c;
-            for (int i = lane; i < KK; i += 64) {
-                const float f = ft[c * KK + i];
-                if (f != 0.0f) {
-                    const int ky = i / KF, kx = i - ky * KF;
-                    ya = min(ya, ky); yb = max(yb, ky); xa = min(xa, kx); xb = max(xb, kx);
-                    const uint32_t u = __float_as_uint(f), e = (u >> 23) & 255u, m = u & 0x7FFFFFu;
-                    if (e == 255u) {
-                        fb = 4095;  // not finite: the double form
-                    } else {
-                        const uint32_t mm = e ? (m | 0x800000u) : m;
-                        const int e0 = (int)(e ? e : 1u) - 150;  // value = mm * 2^e0
-                        fb = max(fb, -(e0 + (int)__builtin_ctz(mm)));
-                        em = max(em, e0 + 31 - (int)__builtin_clz(mm));
-                    }
-                }
-                if (c > 0) neg = neg && (f == -ft[(c - 1) * KK + i]);
-            }
-            // three reductions of 16-bit pairs: (ya, xa) by min, (yb + 1, xb + 1) and
-            // (fraction bits, exponent + 512) by max
-            const uint32_t lo = wave_min_u16x2((uint32_t)ya | ((uint32_t)xa << 16));
-            const uint32_t hi = wave_max_u16x2((uint32_t)(yb + 1) | ((uint32_t)(xb + 1) << 16));
-            const uint32_t ex = wave_max_u16x2((uint32_t)max(fb, 0) | ((uint32_t)(em + 512) << 16));
-            const bool all_neg = __ballot(!neg) == 0;
-            if (lane == 0) {
-                bbox[4 * c] = (int)(lo & 0xFFFFu); bbox[4 * c + 1] = (int)(hi & 0xFFFFu) - 1;
-                bbox[4 * c + 2] = (int)(lo >> 16); bbox[4 * c + 3] = (int)(hi >> 16) - 1;
-                deriv[c] = all_neg ? 1 : 0;
-                if (order_c) s_ex[c] = ex;
-            }
-        }
-        __syncthreads();
-        if (wid == 0) {
-            if (order_c) {  // lane c: channel c
-                // A negated channel is derived only from a computed one: in a run of
-                // channels that each negate the one before, following a channel that
-                // does not, every second one is derived.
-                const bool neg = lane < C && deriv[lane] != 0;
-                const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1;
-                const int c0 = 63 - __clzll(~__ballot(neg) & upto);  // channel 0 never negates
-                const bool der = neg && ((lane - c0) & 1);
-                const bool comp = lane < C && !der;
-                // computed channels in decreasing order of tap area, equal areas by index
-                const int area = comp ? tap_area(bbox, lane) : -1;
-                // the integer form: every computed tap a multiple of 2^-s, |tap| 2^s <
-                // 2^15, and KK * 255 * 2^(exponent + s + 1) < 2^31 bounds every sum
-                const uint32_t ex = comp ? s_ex[lane] : 0u;
-                const uint32_t exm = wave_max_u16x2(comp ? ex : (uint32_t)(112u << 16));  // (-400 + 512) << 16
-                const int sfb = (int)(exm & 0xFFFFu), sem = (int)(exm >> 16) - 512;
-                const bool exact = sfb <= 126 && sem + sfb <= 14 &&
-                                   (sem + sfb + 1 < 0 || ((int64_t)KK * 255 << (sem + sfb + 1)) < (1LL << 31));
-                const int wy = comp ? bbox[4 * lane + 1] - bbox[4 * lane] + 1 : 0;
-                const int wxl = comp ? bbox[4 * lane + 3] - bbox[4 * lane + 2] + 1 : 0;
-                const int size = area <= 0 ? 0 : exact ? ((wy + 1) >> 1) * wxl : area;
-                int rank = 0, off = 0;
-                for (int k = 0; k < C; ++k) {
-                    const int ak = __builtin_amdgcn_readlane(area, k), sk = __builtin_amdgcn_readlane(size, k);
-                    const bool before = ak > area || (ak == area && k < lane);
-                    rank += before;
-                    off += before && ak >= 0 ? sk : 0;
-                }
-                if (lane < C) {
-                    deriv[lane] = der ? 1 : 0;
-                    if (comp) {
-                        order[rank] = lane;
-                        toff[rank] = off;
-                        tstr[rank] = wxl;
-                    }
-                }
-                const int nc = __popcll(__ballot(comp));
-                if (lane == 0) {
-                    s_ncomp = nc;
-                    s_s = exact ? sfb : -1;
-                }
-                if (exact) {
-                    // this wave packs the integer form's taps (int16 pairs of tap rows ky,
-                    // ky + 1; zero past the box), slot after slot, while the others wait
-                    uint32_t *itp = reinterpret_cast<uint32_t *>(r2 + L.itaps);
-                    const int bya = comp ? bbox[4 * lane] : 0, byb = comp ? bbox[4 * lane + 1] : 0;
-                    const int bxa = comp ? bbox[4 * lane + 2] : 0;
-                    for (int k = 0; k < nc; ++k) {
-                        const int c = (int)__builtin_ctzll(__ballot(comp && rank == k));  // slot k's channel
-                        const int ya = __builtin_amdgcn_readlane(bya, c), yb = __builtin_amdgcn_readlane(byb, c);
-                        const int xa = __builtin_amdgcn_readlane(bxa, c), wk = __builtin_amdgcn_readlane(wxl, c);
-                        const int n = ((yb - ya + 2) >> 1) * wk;
-                        uint32_t *tp = itp + __builtin_amdgcn_readlane(off, c);
-                        for (int e = lane; e < n; e += 64) {
-                            const int kp = e / wk, u = e - kp * wk, ky = ya + 2 * kp;
-                            const int q0 = (int)ldexpf(ft[c * KK + ky * KF + xa + u], sfb);
-                            const int q1 = ky + 1 <= yb ? (int)ldexpf(ft[c * KK + (ky + 1) * KF + xa + u], sfb) : 0;
-                            tp[e] = ((uint32_t)q0 & 0xFFFFu) | ((uint32_t)q1 << 16);
-                        }
-                    }
-                }
-            } else {  // every channel computed, in index order, double form with full rows
-                for (int c = lane; c < C; c += 64) {
-                    order[c] = c;
-                    toff[c] = c * KK + max(bbox[4 * c], 0) * KF + max(bbox[4 * c + 2], 0);
-                    tstr[c] = KF;
-                }
-                if (lane == 0) {
-                    s_ncomp = C;
-                    s_s = -1;
-                }
-            }
-        }
-        __syncthreads();
+        // (its first barrier also publishes the staged taps and pixels)
+        analyse_bank(filt, C, KF, BankLds{ft, reinterpret_cast<uint32_t *>(r2 + L.itaps),
+                                          reinterpret_cast<double *>(r2 + L.taps), bbox, deriv, order, toff, tstr, s_ex,
+                                          &s_ncomp, &s_s});
         const int ncomp = s_ncomp, sexp = s_s;
         const bool int_form = sexp >= 0;
-        void *taps = r2 + (int_form ? L.itaps : L.taps);
-        if (!int_form) {  // (the integer form's taps were packed with the order)
-            // per computed channel: its box of taps as doubles (whole rows when C is
-            // large), read from global memory since they replace the staged floats
-            double *tp = reinterpret_cast<double *>(taps);
-            for (int k = 0; k < ncomp; ++k) {
-                const int c = order[k];
-                if (order_c) {
-                    const int ya = bbox[4 * c], xa = bbox[4 * c + 2], wxl = tstr[k];
-                    const int n = max(0, (bbox[4 * c + 1] - ya + 1)) * wxl;
-                    for (int e = tid; e < n; e += ENC_THREADS) {
-                        const int r = e / wxl, u = e - r * wxl;
-                        tp[toff[k] + e] = (double)filt[c * KK + (ya + r) * KF + xa + u];
-                    }
-                } else {
-                    for (int e = tid; e < KK; e += ENC_THREADS) tp[c * KK + e] = (double)filt[c * KK + e];
-                }
-            }
-            __syncthreads();  // (uniform)
-        }
+        const void *taps = r2 + (int_form ? L.itaps : L.taps);
         float *gout = inten_out ? inten_out + (int64_t)b * N : nullptr;
         const FiltCtx fx{H, W, C, Wp, thr, pairs, taps, bbox, deriv, toff, tstr,
                          int_form ? ldexp(1.0, -sexp) : 1.0, Ic, gout};
@@ -1127,6 +1407,140 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void k_encode_small(const uint8_t *
     }
 }
 
+// ------------------------------------------------------------------ filter of large maps
+// The analysed bank in the workspace: BANK_INTS words (ncomp, s, tap words, then
+// box, derived, order, tap offset and row stride per channel), then the taps.
+constexpr int BANK_INTS = 4 + 8 * MAX_DERIV_C;
+constexpr size_t BANK_BYTES = 4096 + 65536;
+static_assert(BANK_INTS * 4 <= 4096, "the bank's integers");
+
+// Workgroup 0 analyses the bank (with `filt`); all clear the `nclear` words of
+// the digit histograms, each its strides of 4 words.
+__global__ __launch_bounds__(ENC_THREADS) void k_enc_prepare(const float *__restrict__ filt, int C, int KF,
+                                                             int *__restrict__ bank, uint32_t *__restrict__ clear,
+                                                             int64_t nclear) {
+    extern __shared__ uint4 lds4[];
+    __shared__ int s_ncomp, s_s, ints[8 * MAX_DERIV_C];
+    __shared__ uint32_t s_ex[MAX_DERIV_C];
+    const int tid = threadIdx.x, KK = KF * KF;
+    const int64_t step = (int64_t)gridDim.x * ENC_THREADS * 4;
+    for (int64_t i = ((int64_t)blockIdx.x * ENC_THREADS + tid) * 4; i < nclear; i += step)
+        *reinterpret_cast<uint4 *>(clear + i) = make_uint4(0, 0, 0, 0);  // (nclear: a multiple of 4)
+    if (blockIdx.x > 0 || !filt) return;
+    unsigned char *m = reinterpret_cast<unsigned char *>(lds4);
+    float *ft = reinterpret_cast<float *>(m);
+    uint32_t *itaps = reinterpret_cast<uint32_t *>(m + up16((size_t)C * KK * sizeof(double)));
+    int *bbox = ints, *deriv = bbox + 4 * C, *order = deriv + C, *toff = order + C, *tstr = toff + C;
+    stage_batched(C * KK, [&](int i) { return filt[i]; }, [&](int i, float v) { ft[i] = v; });
+    analyse_bank(filt, C, KF, BankLds{ft, itaps, reinterpret_cast<double *>(m), bbox, deriv, order, toff, tstr, s_ex,
+                                      &s_ncomp, &s_s});
+    // the last slot's taps end the packed ones (rows of pairs, or of doubles)
+    const int kl = s_ncomp - 1, cl = order[kl];
+    const int wy = max(0, bbox[4 * cl + 1] - bbox[4 * cl] + 1), wx = max(0, bbox[4 * cl + 3] - bbox[4 * cl + 2] + 1);
+    const int words = s_s >= 0 ? toff[kl] + ((wy + 1) >> 1) * wx : 2 * (toff[kl] + wy * wx);
+    const uint32_t *src = s_s >= 0 ? itaps : reinterpret_cast<const uint32_t *>(m);
+    if (tid == 0) {
+        bank[0] = s_ncomp;
+        bank[1] = s_s;
+        bank[2] = words;
+    }
+    for (int i = tid; i < 8 * C; i += ENC_THREADS) bank[4 + i] = ints[i];
+    for (int i = tid; i < words; i += ENC_THREADS) bank[1024 + i] = (int)src[i];
+}
+
+// One workgroup per (image, tile of FT_H x FT_W outputs): the zero-padded tile
+// as vertical pixel pairs and the analysed taps in LDS, then items of 8
+// consecutive outputs of a row of a computed channel (a wave takes 8 rows of
+// 8 items: with the odd row stride their pixel reads fall in distinct banks and
+// their stores are 8 runs of 256 bytes), the channels in decreasing order of tap
+// area.  With `hist`, the positive outputs' first digits are counted on the way.
+// Bound by the sums' instructions: k_filter's double sums took 87 us for 64
+// 160x250 images and 4 filters of 5x5, 100 us for 7 of 241x321 and a DoG bank;
+// this kernel 45 and 29 us, counting included.
+constexpr int FT_H = 32, FT_W = 64;
+__global__ __launch_bounds__(ENC_THREADS) void k_filter_tile(const uint8_t *__restrict__ img, int H, int W, int C,
+                                                             int KF, float thr, int ntx, int nty,
+                                                             const int *__restrict__ bank, float *__restrict__ out,
+                                                             uint32_t *__restrict__ hist) {
+    extern __shared__ uint4 lds4[];
+    __shared__ int ints[8 * MAX_DERIV_C];
+    const int tid = threadIdx.x;
+    const int tx = blockIdx.x % ntx, ty = (blockIdx.x / ntx) % nty, b = blockIdx.x / (ntx * nty);
+    const int x0 = tx * FT_W, y0 = ty * FT_H, p = (KF - 1) / 2;
+    const int rows = min(FT_H, H - y0), Hs = FT_H + KF - 1, Wp = small_filter_wp(FT_W, KF);
+    uint32_t *pairs = reinterpret_cast<uint32_t *>(lds4);
+    uint32_t *h = pairs + (Hs * Wp + 3) / 4 * 4;
+    uint32_t *taps = h + (hist ? RK_BINS / 2 : 0);
+    const int ncomp = bank[0], sexp = bank[1], words = bank[2];
+    const uint8_t *im = img + (int64_t)b * H * W;
+    stage_batched(
+        Hs * Wp,
+        [&](int i) {
+            const int r = i / Wp, xp = i - r * Wp;
+            const int y = y0 + r - p, x = x0 + xp - p;
+            const bool in_x = x >= 0 && x < W;
+            const uint32_t lo = in_x && y >= 0 && y < H ? im[(int64_t)y * W + x] : 0u;
+            const uint32_t hi = in_x && y + 1 >= 0 && y + 1 < H ? im[(int64_t)(y + 1) * W + x] : 0u;
+            return uint2{lo, hi};
+        },
+        [&](int i, uint2 v) {
+            uint32_t hi = v.y;
+            asm volatile("" : "+v"(hi));  // keeps the shift here, out of the load's branch
+            pairs[i] = v.x | hi << 16;
+        });
+    for (int i = tid; i < 8 * C; i += ENC_THREADS) ints[i] = bank[4 + i];
+    for (int i = tid; i < words; i += ENC_THREADS) taps[i] = (uint32_t)bank[1024 + i];
+    if (hist)
+        for (int i = tid; i < RK_BINS / 2; i += ENC_THREADS) h[i] = 0;
+    __syncthreads();
+    const int *bbox = ints, *deriv = bbox + 4 * C, *order = deriv + C, *toff = order + C, *tstr = toff + C;
+    const FiltCtx fx{rows, W, C, Wp, thr, pairs, taps, bbox, deriv, toff, tstr, sexp >= 0 ? ldexp(1.0, -sexp) : 1.0,
+                     nullptr, nullptr};
+    constexpr int PER = FT_H * FT_W / 8;  // items per channel
+    const bool al16 = (W & 3) == 0 && ((uintptr_t)out & 15) == 0;
+    for (int it = tid; it < ncomp * PER; it += ENC_THREADS) {
+        const int slot = it / PER, rem = it - slot * PER;
+        const int y = (rem >> 6) * 8 + ((rem >> 3) & 7), xg = rem & 7;
+        const int nx = min(8, W - x0 - 8 * xg);
+        if (y >= rows || nx <= 0) continue;
+        const int c = order[slot];
+        double val[8];
+        if (sexp >= 0)
+            filter_sums<true>(fx, slot, c, xg, y, val);
+        else
+            filter_sums<false>(fx, slot, c, xg, y, val);
+        float o[8], o2[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float v = (float)val[j], w = v == 0.0f ? 0.0f : -v;
+            o[j] = v < thr ? 0.0f : v;
+            o2[j] = w < thr ? 0.0f : w;
+        }
+        auto put = [&](const float (&q)[8], int cc) {
+            float *dst = out + (((int64_t)b * C + cc) * H + y0 + y) * W + x0 + 8 * xg;
+            if (nx == 8 && al16) {
+                *reinterpret_cast<float4 *>(dst) = float4{q[0], q[1], q[2], q[3]};
+                *reinterpret_cast<float4 *>(dst + 4) = float4{q[4], q[5], q[6], q[7]};
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (j < nx) dst[j] = q[j];
+            }
+            if (hist) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (j < nx) digit_count(h, q[j]);
+            }
+        };
+        put(o, c);
+        if (c + 1 < C && deriv[c + 1]) put(o2, c + 1);
+    }
+    if (hist) {
+        __syncthreads();
+        digit_merge(h, hist + (int64_t)b * RK_BINS);
+    }
+}
+
 // ------------------------------------------------------------------ local normalisation
 // out = in / (float(S / (2r+1)^2) + eps), S the sum of the zero-padded window
 // of the entry's channel taken as row sums R(y', x) (double, dx ascending)
@@ -1221,7 +1635,7 @@ __global__ __launch_bounds__(256) void k_validate_wave(const uint8_t *__restrict
 
 struct EncPlan {
     int64_t N;
-    size_t inten_bytes, bound_bytes, count_bytes;
+    size_t inten_bytes;
 };
 
 int enc_plan(int B, int C, int H, int W, int T, EncPlan &p) {
@@ -1231,27 +1645,54 @@ int enc_plan(int B, int C, int H, int W, int T, EncPlan &p) {
     p.N = (int64_t)C * H * W;
     SPK_REQUIRE(p.N < (1LL << 31), SPK_E_RANGE, "spk_encode_latency: C*H*W too large");
     p.inten_bytes = (size_t)B * p.N * sizeof(float);
-    p.bound_bytes = (size_t)B * (T > 1 ? T - 1 : 1) * sizeof(uint64_t);
-    p.count_bytes = (size_t)B * sizeof(uint32_t);
     return SPK_OK;
 }
 
 size_t small_rank_lds(int64_t N) { return spk::align_up((size_t)N * 4, 16) + small_select_bytes(); }
 
+// The workspace of the large-map rank code (nothing for small maps or T = 1).
+RankWork carve_rank(spk::Carver &cv, int B, int64_t N, int T) {
+    RankWork w{};
+    if (N <= SMALL_MAX || T < 2) return w;
+    w.hist = cv.take<uint32_t>((size_t)B * RK_BINS);
+    w.gmap = cv.take<uint8_t>((size_t)B * RK_BINS);
+    w.cursor = cv.take<uint32_t>((size_t)B * RK_T);
+    w.targ = cv.take<int4>((size_t)B * RK_T);
+    w.list = cv.take<uint64_t>((size_t)B * N);
+    w.bounds = cv.take<uint64_t>((size_t)B * (T - 1));
+    return w;
+}
+
+unsigned clear_blocks(int64_t words) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, words / 4096)); }
+
 // The rank-order code of an intensity map: one workgroup per image when the
-// map has at most SMALL_MAX entries, else the bin boundaries by radix select
-// and a separate expansion.
-void launch_rank(const float *I, int B, int64_t N, int T, uint8_t *t_first, uint8_t *wave, uint64_t *bounds,
-                 uint32_t *count, hipStream_t st) {
+// map has at most SMALL_MAX entries, else boundaries and expansion by many
+// workgroups per image.  counted: the first digits are already in w.hist.
+void launch_rank(const float *I, int B, int64_t N, int T, uint8_t *t_first, uint8_t *wave, const RankWork &w,
+                 bool counted, hipStream_t st) {
     if (N <= SMALL_MAX) {
         hipLaunchKernelGGL(k_encode_small<false>, dim3(B), dim3(ENC_THREADS), small_rank_lds(N), st, nullptr,
                            SmallFilter{}, nullptr, 0.0f, I, (int)N, T, nullptr, t_first, wave);
         return;
     }
-    if (T > 1) hipLaunchKernelGGL(k_rank_select, dim3(B), dim3(SEL_THREADS), 0, st, I, N, T, bounds, count);
-    const int64_t groups = (N + 3) / 4;
-    const int chunks = (int)std::max<int64_t>(1, std::min<int64_t>(64, spk::ceil_div(groups, 256)));
-    hipLaunchKernelGGL(k_expand_latency, dim3((unsigned)(B * chunks)), dim3(256), 0, st, I, N, T, bounds, t_first,
+    if (T > 1) {
+        if (!counted) {
+            const int64_t words = (int64_t)B * RK_BINS;
+            hipLaunchKernelGGL(k_enc_prepare, dim3(clear_blocks(words)), dim3(ENC_THREADS), 0, st, nullptr, 0, 0,
+                               nullptr, w.hist, words);
+            // about 1024 workgroups in all (each merges up to 8192 counters), whole RK_CHUNKs
+            const int64_t want = spk::ceil_div((int64_t)B * N, 1024);
+            const int per = (int)std::min<int64_t>(RK_HIST_MAX, spk::ceil_div(std::max<int64_t>(want, 1), RK_CHUNK) * RK_CHUNK);
+            const int chunks = (int)spk::ceil_div(N, per);
+            hipLaunchKernelGGL(k_rank_hist, dim3((unsigned)(B * chunks)), dim3(256), 0, st, I, N, chunks, per, w.hist);
+        }
+        hipLaunchKernelGGL(k_rank_select, dim3(B), dim3(1024), 0, st, T, w);
+        const int cc = (int)std::min<int64_t>(spk::ceil_div(N, RK_CHUNK), 4096);
+        hipLaunchKernelGGL(k_rank_collect, dim3((unsigned)(B * cc)), dim3(256), 0, st, I, N, cc, w);
+        hipLaunchKernelGGL(k_rank_resolve, dim3((unsigned)(T - 1), (unsigned)B), dim3(256), 0, st, N, T, w);
+    }
+    const int chunks = (int)std::max<int64_t>(1, std::min<int64_t>(1024, spk::ceil_div(N, 16 * 256)));
+    hipLaunchKernelGGL(k_expand_latency, dim3((unsigned)(B * chunks)), dim3(256), 0, st, I, N, T, w.bounds, t_first,
                        wave, chunks);
 }
 
@@ -1262,8 +1703,8 @@ extern "C" size_t spk_encode_latency_workspace_size(int B, int C, int H, int W, 
     if (enc_plan(B, C, H, W, T, p) != SPK_OK) return 0;
     spk::Carver c(nullptr);
     c.take<float>(p.inten_bytes / sizeof(float));
-    c.take<uint64_t>(p.bound_bytes / sizeof(uint64_t));
-    c.take<uint32_t>(p.count_bytes / sizeof(uint32_t));
+    c.take<uint8_t>(BANK_BYTES);
+    carve_rank(c, B, p.N, T);
     return spk::align_up(c.off, 256);
 }
 
@@ -1285,8 +1726,8 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
     hipStream_t st = spk::as_stream(stream);
     spk::Carver cv(workspace);
     float *ws_int = cv.take<float>(p.inten_bytes / sizeof(float));
-    uint64_t *bounds = cv.take<uint64_t>(p.bound_bytes / sizeof(uint64_t));
-    uint32_t *count = cv.take<uint32_t>(p.count_bytes / sizeof(uint32_t));
+    int *bank = reinterpret_cast<int *>(cv.take<uint8_t>(BANK_BYTES));
+    const RankWork rw = carve_rank(cv, B, p.N, T);
     float *I = intensities ? intensities : ws_int;
 
     // rows per band: the whole image when it fits in LDS, else the most that
@@ -1308,15 +1749,32 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
     while (R > 1 && filter_lds(R) > 65536) --R;
     SPK_REQUIRE(filter_lds(R) <= 65536, SPK_E_RANGE, "spk_encode_latency: %d filters of %dx%d on width %d do not fit",
                 C, KF, KF, W);
-    int nb = (H + R - 1) / R;
-    // few images (online steps): more, thinner bands, so that more workgroups share them
-    while ((int64_t)B * nb < 128 && nb < H) nb = std::min(H, 2 * nb);
-    R = (H + nb - 1) / nb;
-    nb = (H + R - 1) / R;  // the kernel's own count: bands of R whole rows may be fewer than asked for
-    hipLaunchKernelGGL(k_filter, dim3((unsigned)(B * nb)), dim3(256), filter_lds(R), st, image, B, H, W, filters, C,
-                       KF, filter_threshold, R, I);
+    bool counted = false;
+    if (C <= MAX_DERIV_C) {
+        // the digits are counted while they are made when 16-bit counters hold a tile's entries
+        const bool rank = (t_first || wave) && p.N > SMALL_MAX && T > 1;
+        counted = rank && C * FT_H * FT_W < 65536;
+        const int64_t words = counted ? (int64_t)B * RK_BINS : 0;
+        const size_t taps_lds = up16((size_t)C * KF * KF * sizeof(double));
+        const size_t itaps_lds = up16((size_t)C * ((KF + 1) / 2) * KF * sizeof(uint32_t));
+        hipLaunchKernelGGL(k_enc_prepare, dim3(clear_blocks(words)), dim3(ENC_THREADS), taps_lds + itaps_lds, st,
+                           filters, C, KF, bank, rw.hist, words);
+        const int ntx = (W + FT_W - 1) / FT_W, nty = (H + FT_H - 1) / FT_H;
+        const size_t lds = up16((size_t)(FT_H + KF - 1) * small_filter_wp(FT_W, KF) * sizeof(uint32_t)) +
+                           (counted ? RK_BINS / 2 * sizeof(uint32_t) : 0) + std::max(taps_lds, itaps_lds);
+        hipLaunchKernelGGL(k_filter_tile, dim3((unsigned)((int64_t)B * ntx * nty)), dim3(ENC_THREADS), lds, st, image,
+                           H, W, C, KF, filter_threshold, ntx, nty, bank, I, counted ? rw.hist : nullptr);
+    } else {
+        int nb = (H + R - 1) / R;
+        // few images (online steps): more, thinner bands, so that more workgroups share them
+        while ((int64_t)B * nb < 128 && nb < H) nb = std::min(H, 2 * nb);
+        R = (H + nb - 1) / nb;
+        nb = (H + R - 1) / R;  // the kernel's own count: bands of R whole rows may be fewer than asked for
+        hipLaunchKernelGGL(k_filter, dim3((unsigned)(B * nb)), dim3(256), filter_lds(R), st, image, B, H, W, filters,
+                           C, KF, filter_threshold, R, I);
+    }
     if (!t_first && !wave) return spk::check_launch("spk_encode_latency");
-    launch_rank(I, B, p.N, T, t_first, wave, bounds, count, st);
+    launch_rank(I, B, p.N, T, t_first, wave, rw, counted, st);
     return spk::check_launch("spk_encode_latency");
 }
 
@@ -1324,9 +1782,8 @@ extern "C" size_t spk_rank_latency_workspace_size(int B, int C, int H, int W, in
     EncPlan p;
     if (enc_plan(B, C, H, W, T, p) != SPK_OK) return 0;
     spk::Carver c(nullptr);
-    c.take<uint64_t>(p.bound_bytes / sizeof(uint64_t));
-    c.take<uint32_t>(p.count_bytes / sizeof(uint32_t));
-    return spk::align_up(c.off, 256);
+    carve_rank(c, B, p.N, T);
+    return spk::align_up(std::max<size_t>(c.off, 1), 256);
 }
 
 extern "C" int spk_rank_latency(const float *intensities, int B, int C, int H, int W, int T, uint8_t *wave,
@@ -1341,9 +1798,8 @@ extern "C" int spk_rank_latency(const float *intensities, int B, int C, int H, i
     SPK_REQUIRE(workspace && ws_bytes >= need, SPK_E_WORKSPACE, "spk_rank_latency: workspace of %zu bytes < %zu required",
                 ws_bytes, need);
     spk::Carver cv(workspace);
-    uint64_t *bounds = cv.take<uint64_t>(p.bound_bytes / sizeof(uint64_t));
-    uint32_t *count = cv.take<uint32_t>(p.count_bytes / sizeof(uint32_t));
-    launch_rank(intensities, B, p.N, T, t_first, wave, bounds, count, spk::as_stream(stream));
+    const RankWork rw = carve_rank(cv, B, p.N, T);
+    launch_rank(intensities, B, p.N, T, t_first, wave, rw, false, spk::as_stream(stream));
     return spk::check_launch("spk_rank_latency");
 }
 

@@ -567,6 +567,76 @@ def test_rank_latency_parity(shape, T):
     assert_equal(host(wave), orc.expand_wave(rtf, T), "wave")
 
 
+# Maps of more than 8192 entries: many workgroups per image.  A first digit's segment is resolved
+# in LDS up to 4096 keys and 1024 with the boundaries' second digits, else by digit passes; the
+# last entries of an image are no whole 16; up to 254 boundaries, in one digit or one per digit.
+RANK_LARGE = [("floats", (2, 4, 60, 61), 30), ("floats", (1, 1, 97, 173), 255), ("flat", (2, 4, 60, 61), 30),
+              ("flat", (1, 3, 53, 53), 255), ("few", (2, 4, 60, 61), 15), ("few", (1, 6, 91, 93), 255),
+              ("narrow", (1, 2, 70, 90), 20), ("narrow", (1, 2, 70, 90), 255), ("sparse", (3, 2, 64, 65), 15),
+              ("extreme", (2, 3, 55, 51), 64), ("floats", (1, 2, 64, 65), 2), ("floats", (2, 2, 64, 65), 1)]
+
+
+def rank_map(kind, g, shape):
+    if kind == "floats":
+        return g.normal(0, 40, shape).astype(np.float32)
+    if kind == "flat":  # one value: the index decides every rank
+        return np.full(shape, 3.25, np.float32)
+    if kind == "few":  # a handful of values, as a binarised image gives: long runs of ties
+        return g.integers(-1, 4, shape).astype(np.float32)
+    if kind == "narrow":  # one first digit, with equal second digits: 1 + m 2^-23, m < 4096
+        return (1.0 + g.integers(0, 4096, shape) * 2.0 ** -23).astype(np.float32)
+    if kind == "sparse":  # image 0 blank, image 1 with one positive entry, image 2 with 7
+        x = -np.abs(g.normal(0, 1, shape)).astype(np.float32)
+        x[1].reshape(-1)[-1] = 0.5
+        x[2].reshape(-1)[11:18] = 2.0
+        return x
+    x = np.exp2(g.integers(-149, 128, shape).astype(np.float64)).astype(np.float32)  # subnormals to 2^127
+    x.reshape(-1)[::97] = np.inf
+    x.reshape(-1)[::89] = -np.inf
+    return x
+
+
+@pytest.mark.parametrize("kind,shape,T", RANK_LARGE)
+def test_rank_latency_large_maps(kind, shape, T):
+    x = rank_map(kind, synth.rng(970 + T, 0), shape)
+    wave, tf = spk.spk_rank_latency(dev(x), T)
+    sync()
+    rtf = orc.rank_latency(x, T)
+    assert_equal(host(tf), rtf, "t_first")
+    assert_equal(host(wave), orc.expand_wave(rtf, T), "wave")
+    # written through addresses of any alignment
+    N = x[0].size
+    sx, stf = dev_shifted(x), dev_shifted(np.zeros(x.shape, np.uint8), 3)
+    swv = dev_shifted(np.zeros((x.shape[0], T) + x.shape[1:], np.uint8), 1)
+    spk.spk_rank_latency(sx, T, wave=swv, t_first=stf)
+    sync()
+    assert N > 8192
+    assert_equal(host(stf), rtf, "t_first, unaligned")
+    assert_equal(host(swv), orc.expand_wave(rtf, T), "wave, unaligned")
+
+
+# Larger maps' filter by tiles of 32x64: ragged tiles, an unaligned width, the double form, banks
+# whose digits are counted in a pass of their own (33 channels) or filtered by bands (65 channels)
+@pytest.mark.parametrize("C,KF,H,W,form", [(6, 13, 33, 65, "int"), (5, 7, 47, 129, "float"), (33, 3, 19, 64, "int"),
+                                           (65, 3, 19, 30, "int"), (4, 31, 70, 71, "float"), (2, 1, 64, 70, "int")])
+def test_encode_large_maps(C, KF, H, W, form):
+    g = synth.rng(480 + C, KF)
+    img = synth.pink_noise_images(g, 2, H, W)
+    if form == "int":
+        bank = (g.integers(-64, 65, (C, KF, KF)) / 64.0).astype(np.float32)
+        bank[C - 1] = -bank[C - 2]  # a derived channel
+    else:
+        bank = (g.normal(0, 1, (C, KF, KF)) * np.exp2(g.integers(-20, 3, (C, KF, KF)))).astype(np.float32)
+    wave, tf, inten = spk.spk_encode_latency(dev(img), dev(bank), 15, 0.5, intensities=None)
+    only = spk.spk_encode_latency(dev(img), dev(bank), 15, 0.5, wave=False, t_first=False, intensities=None)[2]
+    sync()
+    I, rtf, rwave = orc.encode(img, bank, 15, 0.5)
+    assert_equal(host(inten), I, "intensities")
+    assert_equal(host(only), I, "intensities alone")
+    assert_equal(host(tf), rtf, "t_first")
+    assert_equal(host(wave), rwave, "wave")
+
+
 def test_chain_encode_with_local_normalization():
     # filter -> local normalisation (radius 8, the tutorial's) -> rank-order code, against the oracle's steps
     from paper_1903_02440_amd.pipeline import chain_for
