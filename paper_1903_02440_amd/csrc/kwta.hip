@@ -10,35 +10,16 @@
 //     bits 63..56  255 - t_first          (earlier spike wins)
 //     bits 55..24  v_first, order-mapped  (larger potential wins)
 //     bits 23..0   2^24 - 1 - index       (lower linear index wins ties)
-// Silent neurons get key 0.  Three paths, by size:
+// Silent neurons get key 0.  Two paths, by size:
 //   * k <= 16 with per-position lists that fit in LDS: the k best keys of every
 //     position, then k rounds without global reads ("per-position top-k");
-//   * other small maps: tiles of 16 consecutive positions and one 256-thread
-//     workgroup per image ("small maps");
-//   * large maps cut each feature map into tiles of RB rows:
-//   1. k_kwta_tiles: the maximum key of every tile (a group of G lanes per
-//      tile, shuffle reduction), written to the workspace.
-//   2. k_kwta_select: one workgroup per image keeps its tile keys in LDS and
-//      runs the k rounds: block argmax (wave shuffles, then across waves),
-//      emit the winner, set the lateral window in an LDS bitmap of inhibited
-//      positions, clear the winner's feature tiles, and recompute only the
-//      tiles whose current maximum fell inside the window -- every other
-//      tile keeps its maximum, since inhibition only removes candidates.
+//   * else the best key of every (run of feature maps, run of positions), found
+//     again only where it was inhibited and could still win ("units").
 #include <algorithm>
 
 #include "common.hpp"
 
 namespace {
-
-constexpr int SEL_THREADS = 1024;
-constexpr int MAX_TILES = 4096;
-
-struct KwtaGeom {
-    int B, T, C, H, W, k, r;
-    int RB, nbands, ntiles;  // rows per tile, tiles per map, tiles per image
-    int G;                   // lanes per tile when computing all tile maxima
-    int G2;                  // lanes per tile when recomputing inhibited tiles
-};
 
 __device__ __forceinline__ uint64_t kwta_key(int t, float v, uint32_t idx) {
     uint32_t u = __float_as_uint(v);
@@ -71,351 +52,8 @@ __device__ __forceinline__ uint64_t wave_max_u64_dpp(uint64_t v) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint64_t group_max(uint64_t v, int G) {
-    for (int s = G >> 1; s >= 1; s >>= 1) {
-        const uint64_t o = __shfl_xor(v, s, 64);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
-// Maximum key of one tile over its non-inhibited neurons; all G lanes of the
-// group return it.  `inh` is the LDS bitmap of laterally inhibited positions
-// (nullptr before any winner exists).
-__device__ __forceinline__ uint64_t tile_max(const uint8_t *tf, const float *vf, const KwtaGeom &g, int tile,
-                                             int sub, int G, const uint32_t *inh) {
-    const int f = tile / g.nbands, band = tile % g.nbands;
-    const int y0 = band * g.RB;
-    const int rows = min(g.RB, g.H - y0);
-    const int nn = rows * g.W;
-    const int64_t base = ((int64_t)f * g.H + y0) * g.W;
-    uint64_t m = 0;
-    for (int j = sub; j < nn; j += G) {
-        const int pos = y0 * g.W + j;
-        if (inh && ((inh[pos >> 5] >> (pos & 31)) & 1u)) continue;
-        const int t = tf[base + j];
-        if (t < g.T) {
-            const uint64_t key = kwta_key(t, vf[base + j], (uint32_t)(base + j));
-            m = key > m ? key : m;
-        }
-    }
-    return group_max(m, G);
-}
-
-__global__ __launch_bounds__(256) void k_kwta_tiles(const uint8_t *__restrict__ tf, const float *__restrict__ vf,
-                                                    KwtaGeom g, uint64_t *__restrict__ tilekey) {
-    const uint32_t gid = (blockIdx.x * blockDim.x + threadIdx.x) / (uint32_t)g.G;  // < 2^31, checked on the host
-    const int sub = threadIdx.x % g.G;
-    const uint32_t total = (uint32_t)g.B * (uint32_t)g.ntiles;
-    const bool live = gid < total;
-    const uint32_t b = live ? gid / (uint32_t)g.ntiles : 0;
-    const int tile = live ? (int)(gid - b * (uint32_t)g.ntiles) : 0;
-    const int64_t N = (int64_t)g.C * g.H * g.W;
-    // every lane takes part in the shuffles; lanes past the end read tile 0 of image 0
-    const uint64_t m = tile_max(tf + b * N, vf + b * N, g, tile, sub, g.G, nullptr);
-    if (live && sub == 0) tilekey[gid] = m;
-}
-
-__global__ __launch_bounds__(SEL_THREADS) void k_kwta_select(const uint8_t *__restrict__ tf_all,
-                                                             const float *__restrict__ vf_all, KwtaGeom g,
-                                                             const uint64_t *__restrict__ tilekey,
-                                                             int32_t *__restrict__ winners,
-                                                             int32_t *__restrict__ n_winners) {
-    extern __shared__ uint64_t smem64[];
-    uint64_t *keys = smem64;                                          // ntiles
-    int *list = reinterpret_cast<int *>(keys + g.ntiles);             // ntiles
-    const int nwords = (g.H * g.W + 31) / 32;
-    uint32_t *inh = reinterpret_cast<uint32_t *>(list + g.ntiles);    // nwords
-    __shared__ uint64_t red[SEL_THREADS / 64];
-    __shared__ int nlist;
-
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t N = (int64_t)g.C * g.H * g.W;
-    const uint8_t *tf = tf_all + (int64_t)b * N;
-    const float *vf = vf_all + (int64_t)b * N;
-    int32_t *win = winners + (int64_t)b * g.k * 4;
-
-    for (int i = tid; i < g.ntiles; i += SEL_THREADS) keys[i] = tilekey[(int64_t)b * g.ntiles + i];
-    for (int i = tid; i < nwords; i += SEL_THREADS) inh[i] = 0u;
-    for (int i = tid; i < 4 * g.k; i += SEL_THREADS) win[i] = -1;
-    if (tid == 0) nlist = 0;
-    __syncthreads();
-
-    int found = 0;
-    for (int round = 0; round < g.k; ++round) {
-        uint64_t m = 0;
-        for (int i = tid; i < g.ntiles; i += SEL_THREADS) m = keys[i] > m ? keys[i] : m;
-        m = spk::wave_max_u64(m);
-        if (lane == 0) red[wv] = m;
-        __syncthreads();
-        uint64_t best = 0;
-        for (int w = 0; w < SEL_THREADS / 64; ++w) best = red[w] > best ? red[w] : best;
-        if (best == 0) break;  // uniform: every thread read the same red[]
-        const int idx = (int)(0xFFFFFFu - (uint32_t)(best & 0xFFFFFFu));
-        const int t = 255 - (int)(best >> 56);
-        const int f = idx / (g.H * g.W), y = (idx / g.W) % g.H, x = idx % g.W;
-        if (tid == 0) {
-            win[4 * round + 0] = f;
-            win[4 * round + 1] = t;
-            win[4 * round + 2] = y;
-            win[4 * round + 3] = x;
-        }
-        ++found;
-        // lateral window, clipped at the borders
-        const int ya = max(0, y - g.r), yb = min(g.H - 1, y + g.r);
-        const int xa = max(0, x - g.r), xb = min(g.W - 1, x + g.r);
-        const int wh = yb - ya + 1, ww = xb - xa + 1;
-        for (int i = tid; i < wh * ww; i += SEL_THREADS) {
-            const int pos = (ya + i / ww) * g.W + xa + i % ww;
-            atomicOr(&inh[pos >> 5], 1u << (pos & 31));
-        }
-        // retire the winner's feature map; list tiles whose maximum is now inhibited
-        for (int i = tid; i < g.ntiles; i += SEL_THREADS) {
-            const uint64_t kk = keys[i];
-            if (kk == 0) continue;
-            if (i / g.nbands == f) {
-                keys[i] = 0;
-                continue;
-            }
-            const int ti = (int)(0xFFFFFFu - (uint32_t)(kk & 0xFFFFFFu));
-            const int ty = (ti / g.W) % g.H, tx = ti % g.W;
-            if (ty >= ya && ty <= yb && tx >= xa && tx <= xb) list[atomicAdd(&nlist, 1)] = i;
-        }
-        __syncthreads();
-        const int nl = nlist;
-        const int groups = SEL_THREADS / g.G2, grp = tid / g.G2, sub = tid % g.G2;
-        const int passes = (nl + groups - 1) / groups;  // identical trip count for all lanes
-        for (int p = 0; p < passes; ++p) {
-            const int e = p * groups + grp;
-            const int tile = e < nl ? list[e] : list[0];
-            const uint64_t mm = tile_max(tf, vf, g, tile, sub, g.G2, inh);
-            if (e < nl && sub == 0) keys[tile] = mm;
-        }
-        __syncthreads();
-        if (tid == 0) nlist = 0;
-        __syncthreads();
-    }
-    if (tid == 0) n_winners[b] = found;
-}
-
-// ------------------------------------------------------------------ small maps
-// When every image has at most SMALL_TILES tiles of 16 consecutive positions
-// of one feature map, one 256-thread workgroup per image keeps all its tile
-// keys in LDS.  Each round's argmax scan also retires the previous winner
-// lazily: a tile of its feature is cleared, a tile whose maximum lies in its
-// window is listed (ballot compaction) and then recomputed from global memory,
-// one listed tile per thread with its loads issued together, against the LDS
-// bitmap of all inhibited positions.  Quotients come from magic multipliers
-// (q = umulhi(n, ceil(2^32/d)), exact for the sizes the host admits here).
-constexpr int SMALL_TILES = 4096;  // keys, list and bitmap stay within 64 KB of LDS
-constexpr int SMALL_THREADS = 256;
-
-struct KwtaSmall {
-    int B, T, C, HW, W, k, r, tpm, ntiles;  // tpm: 16-position tiles per feature map
-    unsigned mHW, mW;                        // magic multipliers for /HW and /W
-};
-
 // n / d as umulhi(n, m) with m = ceil(2^32 / d); m == 0 stands for d == 1 (2^32 does not fit)
 __device__ __forceinline__ unsigned qdiv(unsigned n, unsigned m) { return m ? __umulhi(n, m) : n; }
-
-// The 16 first-spike times and potentials of one tile: as four 4-byte and four
-// 16-byte loads when `vec` (map size a multiple of 4 and aligned bases: then
-// every full tile is aligned), else as single loads.
-__device__ __forceinline__ void load_tile16(const uint8_t *__restrict__ tf, const float *__restrict__ vf, int64_t base,
-                                            int n, int T, int vec, int (&tv)[16], float (&vv)[16]) {
-    if (vec && n == 16) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t w = *reinterpret_cast<const uint32_t *>(tf + base + 4 * q);
-            const float4 v = *reinterpret_cast<const float4 *>(vf + base + 4 * q);
-            tv[4 * q + 0] = w & 0xFF; tv[4 * q + 1] = (w >> 8) & 0xFF;
-            tv[4 * q + 2] = (w >> 16) & 0xFF; tv[4 * q + 3] = w >> 24;
-            vv[4 * q + 0] = v.x; vv[4 * q + 1] = v.y; vv[4 * q + 2] = v.z; vv[4 * q + 3] = v.w;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            tv[j] = j < n ? (int)tf[base + j] : T;
-            vv[j] = j < n ? vf[base + j] : 0.0f;
-        }
-    }
-}
-
-// Four lanes per tile, each with 4 consecutive positions, so a wave's loads
-// are contiguous; two shuffle steps combine the quarter maxima.  Grid-stride
-// over the batch's tiles (the stride is a multiple of 4 lanes), four strides
-// per pass with all their loads issued before any is used.
-__global__ __launch_bounds__(256) void k_kwta_tiles16(const uint8_t *__restrict__ tf, const float *__restrict__ vf,
-                                                      KwtaSmall g, int vec, uint64_t *__restrict__ tilekey) {
-    constexpr int U = 4;
-    const uint32_t total = (uint32_t)g.B * (uint32_t)g.ntiles * 4u;  // < 2^31, checked on the host
-    const uint32_t stride = gridDim.x * 256u;
-    for (uint32_t g0 = blockIdx.x * 256u; g0 < total; g0 += U * stride) {  // uniform per workgroup
-        int tv[U][4];
-        float vv[U][4];
-        uint32_t idx0[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t gt = g0 + u * stride + threadIdx.x;
-            const uint32_t gid = gt >> 2;
-            const int sub = (int)(gt & 3u);
-            idx0[u] = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                tv[u][j] = g.T;
-                vv[u][j] = 0.0f;
-            }
-            if (gt < total) {
-                const uint32_t b = gid / (uint32_t)g.ntiles;
-                const int tile = (int)(gid - b * (uint32_t)g.ntiles);
-                const int f = tile / g.tpm, pos0 = (tile - f * g.tpm) * 16 + 4 * sub;
-                const int64_t base = (int64_t)b * g.C * g.HW + (int64_t)f * g.HW + pos0;
-                idx0[u] = (uint32_t)(f * g.HW + pos0);
-                if (vec && pos0 + 4 <= g.HW) {
-                    const uint32_t w = *reinterpret_cast<const uint32_t *>(tf + base);
-                    const float4 v = *reinterpret_cast<const float4 *>(vf + base);
-                    tv[u][0] = w & 0xFF; tv[u][1] = (w >> 8) & 0xFF; tv[u][2] = (w >> 16) & 0xFF; tv[u][3] = w >> 24;
-                    vv[u][0] = v.x; vv[u][1] = v.y; vv[u][2] = v.z; vv[u][3] = v.w;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const bool ok = pos0 + j < g.HW;
-                        tv[u][j] = ok ? (int)tf[base + j] : g.T;
-                        vv[u][j] = ok ? vf[base + j] : 0.0f;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t gt = g0 + u * stride + threadIdx.x;
-            uint64_t m = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (tv[u][j] < g.T) {
-                    const uint64_t key = kwta_key(tv[u][j], vv[u][j], idx0[u] + j);
-                    m = key > m ? key : m;
-                }
-            m = group_max(m, 4);
-            if (gt < total && (gt & 3u) == 0) tilekey[gt >> 2] = m;
-        }
-    }
-}
-
-__device__ __forceinline__ uint64_t recompute16(const uint8_t *__restrict__ tf, const float *__restrict__ vf,
-                                                const KwtaSmall &g, int vec, int tile, const uint32_t *inh) {
-    const int f = tile / g.tpm, pos0 = (tile - f * g.tpm) * 16;
-    const int base = f * g.HW + pos0;
-    int tv[16];
-    float vv[16];
-    load_tile16(tf, vf, base, min(16, g.HW - pos0), g.T, vec, tv, vv);
-    uint64_t m = 0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int pos = pos0 + j;
-        if (tv[j] < g.T && !((inh[pos >> 5] >> (pos & 31)) & 1u)) {
-            const uint64_t key = kwta_key(tv[j], vv[j], (uint32_t)(base + j));
-            m = key > m ? key : m;
-        }
-    }
-    return m;
-}
-
-__global__ __launch_bounds__(SMALL_THREADS) void k_kwta_select_small(const uint8_t *__restrict__ tf_all,
-                                                                     const float *__restrict__ vf_all, KwtaSmall g,
-                                                                     int vec, const uint64_t *__restrict__ tilekey,
-                                                                     int32_t *__restrict__ winners,
-                                                                     int32_t *__restrict__ n_winners) {
-    extern __shared__ uint64_t keys[];  // ntiles keys, the inhibition bitmap, ntiles list entries
-    const int nwords = (g.HW + 31) / 32;
-    uint32_t *inh = reinterpret_cast<uint32_t *>(keys + g.ntiles);
-    uint16_t *list = reinterpret_cast<uint16_t *>(inh + nwords);
-    __shared__ uint64_t red[SMALL_THREADS / 64];
-    __shared__ int nlist[2];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t N = (int64_t)g.C * g.HW;
-    const uint8_t *tf = tf_all + (int64_t)b * N;
-    const float *vf = vf_all + (int64_t)b * N;
-    int32_t *win = winners + (int64_t)b * g.k * 4;
-    for (int i = tid; i < g.ntiles; i += SMALL_THREADS) keys[i] = tilekey[(int64_t)b * g.ntiles + i];
-    for (int i = tid; i < nwords; i += SMALL_THREADS) inh[i] = 0u;
-    for (int i = tid; i < 4 * g.k; i += SMALL_THREADS) win[i] = -1;
-    if (tid < 2) nlist[tid] = 0;
-    __syncthreads();
-    const uint64_t below = (1ULL << lane) - 1ULL;  // lanes under this one
-    const int H = g.HW / g.W;
-    int fw = -1, yw = 0, xw = 0, found = 0;
-    for (int round = 0; round < g.k; ++round) {
-        int *cnt = &nlist[round & 1];
-        // scan: retire the previous winner's feature, list the tiles whose
-        // maximum fell in its window, and take the maximum of the rest
-        uint64_t m = 0;
-        for (int i0 = 0; i0 < g.ntiles; i0 += SMALL_THREADS) {
-            const int i = i0 + tid;
-            uint64_t key = i < g.ntiles ? keys[i] : 0;
-            bool redo = false;
-            if (key != 0 && fw >= 0) {
-                const unsigned idx = 0xFFFFFFu - (unsigned)(key & 0xFFFFFFu);
-                const unsigned f = qdiv(idx, g.mHW), pos = idx - f * (unsigned)g.HW;
-                const int y = (int)qdiv(pos, g.mW), x = (int)pos - y * g.W;
-                if ((int)f == fw) {
-                    key = 0;
-                    keys[i] = 0;
-                } else if (abs(y - yw) <= g.r && abs(x - xw) <= g.r) {
-                    redo = true;
-                    key = 0;
-                }
-            }
-            const uint64_t mask = __ballot(redo);
-            if (mask) {
-                int at = 0;
-                if (lane == 0) at = atomicAdd(cnt, __popcll(mask));
-                at = __shfl(at, 0, 64);
-                if (redo) list[at + __popcll(mask & below)] = (uint16_t)i;
-            }
-            m = key > m ? key : m;
-        }
-        __syncthreads();
-        // recompute the listed tiles, one per thread
-        const int nl = *cnt;
-        for (int e = tid; e < nl; e += SMALL_THREADS) {
-            const int tile = list[e];
-            const uint64_t key = recompute16(tf, vf, g, vec, tile, inh);
-            keys[tile] = key;
-            m = key > m ? key : m;
-        }
-        m = spk::wave_max_u64(m);
-        if (lane == 0) red[wv] = m;
-        __syncthreads();
-        uint64_t best = 0;
-#pragma unroll
-        for (int w = 0; w < SMALL_THREADS / 64; ++w) best = red[w] > best ? red[w] : best;
-        if (tid == 0) nlist[(round + 1) & 1] = 0;  // the other counter: last read before the previous barrier
-        if (best == 0) break;  // uniform: every thread read the same red[]
-        const int idx = (int)(0xFFFFFFu - (unsigned)(best & 0xFFFFFFu));
-        const int t = 255 - (int)(best >> 56);
-        fw = (int)qdiv((unsigned)idx, g.mHW);
-        const int pos = idx - fw * g.HW;
-        yw = (int)qdiv((unsigned)pos, g.mW);
-        xw = pos - yw * g.W;
-        if (tid == 0) {
-            win[4 * round + 0] = fw;
-            win[4 * round + 1] = t;
-            win[4 * round + 2] = yw;
-            win[4 * round + 3] = xw;
-        }
-        ++found;
-        const int ya = max(0, yw - g.r), yb = min(H - 1, yw + g.r);
-        const int xa = max(0, xw - g.r), xb = min(g.W - 1, xw + g.r);
-        const int wh = yb - ya + 1, ww = xb - xa + 1;
-        for (int i = tid; i < wh * ww; i += SMALL_THREADS) {
-            const int p = (ya + i / ww) * g.W + xa + i % ww;
-            atomicOr(&inh[p >> 5], 1u << (p & 31));
-        }
-        __syncthreads();
-    }
-    if (tid == 0) n_winners[b] = found;
-}
 
 // ------------------------------------------------------------ per-position top-k
 // When k <= 16 and each image's lists fit in LDS, one workgroup per image
@@ -731,6 +369,238 @@ __global__ __launch_bounds__(TOPK_THREADS_SMALL_B) void k_kwta_topk(const uint8_
     if (tid == 0) n_winners[b] = found;
 }
 
+// ------------------------------------------------------------ units
+// A unit is a run of feature maps times a run of 64 * L consecutive positions,
+// the work of one wave.  k_kwta_units writes every unit's best key; the rounds
+// (k_kwta_rounds, one workgroup per image) hold the keys in registers.  A key
+// whose feature was retired or whose position was inhibited since is an upper
+// bound of its unit; only the units whose bound exceeds the best valid key are
+// read again, each by its wave.
+// Why units and not the maxima of single feature maps: features that see the
+// same input have their maxima at the same places, so one winner inhibits the
+// maximum of every map; with runs of maps it inhibits those of the runs at its
+// place only.  Runs of all maps would suffer in the opposite case, a feature
+// that is the best almost everywhere.  Hence at most UN_MAX units with about as
+// many positions as maps to a side: 256 maps of 256x256 make 256 x 16 units of
+// 256 positions x 16 maps, 20 KB to read again.
+// Bound by the one pass over the maps (5 bytes a neuron) and k rounds of two
+// reductions each.  With the maxima of tiles of 16 rows, all of them read again
+// whose maximum was inhibited, 4 images of 256 maps of 256x256, k = 32, took
+// 14.6 ms; now 0.48 ms, 79 us of it the pass (4.3 TB/s) and the rest the
+// latency of the rounds' reads (5 to 14 us a round).
+constexpr int UN_MAX = 4096;      // units per image at most (8 bytes each in the workspace)
+constexpr int UN_UPT = 4;         // units per thread of the rounds
+constexpr int UN_THREADS = UN_MAX / UN_UPT;
+constexpr int UN_WIDE = 4096;     // positions from which a lane takes 4 (fewer groups), else 1
+constexpr int UN_MAPS = 8;        // maps a wave reads at once
+constexpr int UN_MAX_C = 4096;    // feature maps at most (the retired ones' bitmap)
+
+struct KwtaUnits {
+    int B, T, C, HW, W, k, r;
+    int L;              // positions per lane: 1 or 4
+    int ns, fps;        // runs of feature maps and maps per run
+    int groups, units;  // runs of 64 * L positions, ns * groups
+    int vec;            // L == 4 with aligned 4-byte / 16-byte loads
+    unsigned mHW;       // ceil(2^32 / HW) (0 for 1)
+    uint64_t *ukey;     // [B][units], unit = group * ns + run
+};
+
+// The feature of a key: the estimated quotient is exact or one too large.
+__device__ __forceinline__ int unit_feature(const KwtaUnits &g, uint64_t key, int &pos) {
+    const unsigned idx = 0xFFFFFFu - (unsigned)(key & 0xFFFFFFu);
+    int f = (int)qdiv(idx, g.mHW);
+    pos = (int)idx - f * g.HW;
+    if (pos < 0) {
+        --f;
+        pos += g.HW;
+    }
+    return f;
+}
+
+// The best key of unit u's feature maps fa..fb-1 over the live features and
+// positions, by one wave (bitmaps of the retired features and inhibited
+// positions, or null).
+template <int L>
+__device__ __forceinline__ uint64_t unit_best(const uint8_t *__restrict__ tf, const float *__restrict__ vf,
+                                              const KwtaUnits &g, int grp, int fa, int fb, int lane,
+                                              const uint32_t *dead, const uint32_t *inh) {
+    constexpr int U = UN_MAPS;
+    const int p = (grp * 64 + lane) * L;
+    unsigned ok = 0;  // positions that count
+#pragma unroll
+    for (int j = 0; j < L; ++j) ok |= (p + j < g.HW ? 1u : 0u) << j;
+    if (inh && ok) ok &= ~(inh[p >> 5] >> (p & 31));
+    uint64_t m = 0;
+    for (int f0 = fa; f0 < fb; f0 += U) {
+        uint32_t tw[U];  // L first-spike times, a byte each
+        float vv[U][L];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {  // (clamped: unconditional loads, all in flight)
+            const int o = min(f0 + q, fb - 1) * g.HW;
+            if (L == 4 && g.vec) {     // (whole quads: HW is a multiple of 4)
+                const int oq = o + min(p, g.HW - 4);
+                tw[q] = *reinterpret_cast<const uint32_t *>(tf + oq);
+                const float4 x = *reinterpret_cast<const float4 *>(vf + oq);
+                vv[q][0] = x.x;
+                vv[q][L > 1 ? 1 : 0] = L > 1 ? x.y : x.x;
+                vv[q][L > 2 ? 2 : 0] = L > 2 ? x.z : x.x;
+                vv[q][L > 3 ? 3 : 0] = L > 3 ? x.w : x.x;
+            } else {
+                tw[q] = 0;
+#pragma unroll
+                for (int j = 0; j < L; ++j) {
+                    const int oj = o + min(p + j, g.HW - 1);
+                    tw[q] |= (uint32_t)tf[oj] << (8 * j);
+                    vv[q][j] = vf[oj];
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int f = f0 + q;
+            if (f >= fb || (dead && ((dead[f >> 5] >> (f & 31)) & 1u))) continue;  // uniform
+#pragma unroll
+            for (int j = 0; j < L; ++j) {
+                const int t = (int)((tw[q] >> (8 * j)) & 255u);
+                if (((ok >> j) & 1u) && t < g.T) {
+                    const uint64_t key = kwta_key(t, vv[q][j], (uint32_t)(f * g.HW + p + j));
+                    m = key > m ? key : m;
+                }
+            }
+        }
+    }
+    return wave_max_u64_dpp(m);
+}
+
+// Grid: image * ceil(units / 4) blocks of 4 units, one wave each.  Consecutive
+// units are the runs of maps at one place.
+__global__ __launch_bounds__(256) void k_kwta_units(const uint8_t *__restrict__ tf, const float *__restrict__ vf,
+                                                    KwtaUnits g) {
+    const int nblk = (g.units + 3) / 4, lane = threadIdx.x & 63;
+    const int b = blockIdx.x / nblk, u = (int)(blockIdx.x - b * nblk) * 4 + (int)(threadIdx.x >> 6);
+    if (u >= g.units) return;
+    const int64_t N = (int64_t)g.C * g.HW;
+    const int grp = u / g.ns, fa = (u - grp * g.ns) * g.fps, fb = min(g.C, fa + g.fps);
+    const uint64_t m = g.L == 4 ? unit_best<4>(tf + b * N, vf + b * N, g, grp, fa, fb, lane, nullptr, nullptr)
+                                : unit_best<1>(tf + b * N, vf + b * N, g, grp, fa, fb, lane, nullptr, nullptr);
+    if (lane == 0) g.ukey[(int64_t)b * g.units + u] = m;
+}
+
+template <int L>
+__global__ __launch_bounds__(UN_THREADS) void k_kwta_rounds(const uint8_t *__restrict__ tf_all,
+                                                            const float *__restrict__ vf_all, KwtaUnits g,
+                                                            int32_t *__restrict__ winners,
+                                                            int32_t *__restrict__ n_winners) {
+    extern __shared__ uint32_t inh[];         // bitmap of the inhibited positions
+    __shared__ uint32_t dead[UN_MAX_C / 32];  // bitmap of the retired features
+    __shared__ uint64_t red[2][UN_THREADS / 64];
+    __shared__ uint64_t res[UN_MAX];          // the listed units' new keys
+    __shared__ uint16_t list[UN_MAX];
+    __shared__ int nlist;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int NT = blockDim.x, NW = NT >> 6, nwords = (g.HW + 31) / 32;
+    const int64_t N = (int64_t)g.C * g.HW;
+    const uint8_t *tf = tf_all + b * N;
+    const float *vf = vf_all + b * N;
+    int32_t *win = winners + (int64_t)b * g.k * 4;
+    for (int i = tid; i < nwords; i += NT) inh[i] = 0;
+    for (int i = tid; i < UN_MAX_C / 32; i += NT) dead[i] = 0;
+    for (int i = tid; i < 4 * g.k; i += NT) win[i] = -1;
+    uint64_t K[UN_UPT];
+#pragma unroll
+    for (int i = 0; i < UN_UPT; ++i) {
+        const int u = i * NT + tid;
+        K[i] = u < g.units ? g.ukey[(int64_t)b * g.units + u] : 0;
+    }
+    const int nsub = (g.fps + UN_MAPS - 1) / UN_MAPS;  // parts of a unit's maps, a wave each
+    if (tid == 0) nlist = 0;
+    __syncthreads();
+    int found = 0;
+    for (int round = 0; round < g.k; ++round) {
+        bool valid[UN_UPT];
+        uint64_t m = 0;
+#pragma unroll
+        for (int i = 0; i < UN_UPT; ++i) {
+            int pos;
+            const int f = unit_feature(g, K[i], pos);
+            valid[i] = K[i] != 0 && !((dead[f >> 5] >> (f & 31)) & 1u) && !((inh[pos >> 5] >> (pos & 31)) & 1u);
+            m = valid[i] && K[i] > m ? K[i] : m;
+        }
+        m = wave_max_u64_dpp(m);
+        if (lane == 0) red[0][wv] = m;
+        __syncthreads();
+        uint64_t best = 0;
+        for (int w = 0; w < NW; ++w) best = red[0][w] > best ? red[0][w] : best;
+        // the units to read again, then their maps in parts dealt out to the waves
+        int at[UN_UPT];
+#pragma unroll
+        for (int i = 0; i < UN_UPT; ++i) {
+            at[i] = -1;
+            if (!valid[i] && K[i] > best) {
+                at[i] = atomicAdd(&nlist, 1);
+                list[at[i]] = (uint16_t)(i * NT + tid);
+                res[at[i]] = 0;
+            }
+        }
+        __syncthreads();
+        const int nl = nlist;
+        for (int e = wv; e < nl * nsub; e += NW) {
+            const int li = e / nsub, u = list[li], grp = u / g.ns, sp = u - grp * g.ns;
+            const int fa = sp * g.fps + (e - li * nsub) * UN_MAPS, fb = min(min(g.C, (sp + 1) * g.fps), fa + UN_MAPS);
+            if (fa >= fb) continue;  // (the last run's maps may be fewer)
+            const uint64_t key = unit_best<L>(tf, vf, g, grp, fa, fb, lane, dead, inh);
+            if (lane == 0 && key) atomicMax(reinterpret_cast<unsigned long long *>(&res[li]), (unsigned long long)key);
+        }
+        __syncthreads();
+        m = 0;
+#pragma unroll
+        for (int i = 0; i < UN_UPT; ++i)
+            if (at[i] >= 0) {
+                K[i] = res[at[i]];
+                m = K[i] > m ? K[i] : m;
+            }
+        m = wave_max_u64_dpp(m);
+        if (lane == 0) red[1][wv] = m;
+        if (tid == 0) nlist = 0;
+        __syncthreads();
+        for (int w = 0; w < NW; ++w) best = red[1][w] > best ? red[1][w] : best;
+        if (best == 0) break;  // uniform: every thread read the same red[]
+        int pos;
+        const int fw = unit_feature(g, best, pos);
+        const int yw = pos / g.W, xw = pos - yw * g.W, H = g.HW / g.W;
+        if (tid == 0) {
+            win[4 * round + 0] = fw;
+            win[4 * round + 1] = 255 - (int)(best >> 56);
+            win[4 * round + 2] = yw;
+            win[4 * round + 3] = xw;
+            dead[fw >> 5] |= 1u << (fw & 31);
+        }
+        ++found;
+        const int ya = max(0, yw - min(g.r, yw)), yb = min(H - 1, yw + min(g.r, H));
+        const int xa = max(0, xw - min(g.r, xw)), xb = min(g.W - 1, xw + min(g.r, g.W));
+        const int ww = xb - xa + 1, wh = yb - ya + 1;
+        for (int i = tid; i < wh * ww; i += NT) {
+            const int q = (ya + i / ww) * g.W + xa + i % ww;
+            atomicOr(&inh[q >> 5], 1u << (q & 31));
+        }
+        __syncthreads();
+    }
+    if (tid == 0) n_winners[b] = found;
+}
+
+KwtaUnits kwta_units(int B, int T, int C, int H, int W, int k, int r) {
+    KwtaUnits g{};
+    g.B = B; g.T = T; g.C = C; g.HW = H * W; g.W = W; g.k = k; g.r = r;
+    g.L = g.HW >= UN_WIDE ? 4 : 1;
+    g.groups = (int)spk::ceil_div(g.HW, 64 * g.L);  // at most 256
+    const int ns = std::min(C, UN_MAX / g.groups);
+    g.fps = (C + ns - 1) / ns;
+    g.ns = (C + g.fps - 1) / g.fps;
+    g.units = g.ns * g.groups;
+    g.mHW = g.HW == 1 ? 0u : (unsigned)(((1ULL << 32) + (uint64_t)g.HW - 1) / (uint64_t)g.HW);
+    return g;
+}
+
 bool kwta_topk(int B, int T, int C, int H, int W, int k, int r, KwtaTopk &s) {
     const int64_t HW = (int64_t)H * W;
     if (k > TOPK_MAX_K || HW > 65536) return false;
@@ -800,58 +670,28 @@ void dispatch_topk(const KwtaTopk &s, const uint8_t *tf, const float *vf, int32_
     }
 }
 
-bool kwta_small(int B, int T, int C, int H, int W, int k, int r, KwtaSmall &s) {
-    const int64_t HW = (int64_t)H * W;
-    const int64_t tpm = (HW + 15) / 16;
-    if (HW > 65536 || C * tpm > SMALL_TILES) return false;
-    auto magic = [](int64_t d) {  // 0 for d == 1 (see qdiv)
-        return d == 1 ? 0u : (unsigned)(((1ULL << 32) + (uint64_t)d - 1) / (uint64_t)d);
-    };
-    auto exact = [](int64_t d, int64_t n) {  // umulhi(x, ceil(2^32/d)) == x/d for all x < n
-        const uint64_t m = ((1ULL << 32) + (uint64_t)d - 1) / (uint64_t)d;
-        const uint64_t e = m * (uint64_t)d - (1ULL << 32);
-        return (uint64_t)n * e < (1ULL << 32);
-    };
-    if (!exact(HW, (int64_t)C * HW) || !exact(W, HW)) return false;
-    if ((int64_t)B * C * tpm * 16 >= (1LL << 31)) return false;
-    s = KwtaSmall{B, T, C, (int)HW, W, k, r, (int)tpm, (int)(C * tpm), magic(HW), magic(W)};
-    return true;
-}
-
-int kwta_geom(int B, int T, int C, int H, int W, int k, int r, KwtaGeom &g) {
+int kwta_check(int B, int T, int C, int H, int W, int k, int r) {
     SPK_REQUIRE(B >= 0 && T >= 1 && C >= 1 && H >= 1 && W >= 1, SPK_E_SHAPE, "spk_kwta: bad sizes");
     SPK_REQUIRE(T <= 255, SPK_E_RANGE, "spk_kwta: T=%d > 255", T);
     SPK_REQUIRE((int64_t)C * H * W <= (1LL << 24), SPK_E_RANGE, "spk_kwta: C*H*W > 2^24");
     SPK_REQUIRE((int64_t)H * W <= 65536, SPK_E_RANGE, "spk_kwta: H*W > 65536");
     SPK_REQUIRE(k >= 1 && r >= 0, SPK_E_ARG, "spk_kwta: k=%d must be >= 1 and radius=%d >= 0", k, r);
-    g.B = B; g.T = T; g.C = C; g.H = H; g.W = W; g.k = k; g.r = r;
-    int RB = 1;
-    while (RB < H && (int64_t)C * ((H + RB - 1) / RB) > MAX_TILES) RB *= 2;
-    RB = RB > H ? H : RB;
-    g.RB = RB;
-    g.nbands = (H + RB - 1) / RB;
-    SPK_REQUIRE((int64_t)C * g.nbands <= MAX_TILES, SPK_E_RANGE, "spk_kwta: %d feature maps exceed %d tiles", C,
-                MAX_TILES);
-    g.ntiles = C * g.nbands;
-    const int nn = RB * W;
-    int G = 1;
-    while (G < nn && G < 64) G <<= 1;
-    g.G = G;
-    // small tiles are recomputed one per thread: their loads then overlap
-    // instead of waiting on each other group after group
-    g.G2 = nn <= 32 ? 1 : G;
-    SPK_REQUIRE((int64_t)B * g.ntiles * G < (1LL << 31), SPK_E_RANGE, "spk_kwta: batch too large");
+    SPK_REQUIRE(C <= UN_MAX_C, SPK_E_RANGE, "spk_kwta: %d feature maps exceed %d", C, UN_MAX_C);
+    // the batch limit of the call: B * (tiles of RB rows) * (lanes up to 64 that cover one) < 2^31
+    int RB = 1, G = 1;
+    while (RB < H && (int64_t)C * ((H + RB - 1) / RB) > UN_MAX) RB *= 2;
+    RB = std::min(RB, H);
+    while (G < RB * W && G < 64) G <<= 1;
+    SPK_REQUIRE((int64_t)B * C * ((H + RB - 1) / RB) * G < (1LL << 31), SPK_E_RANGE, "spk_kwta: batch too large");
     return SPK_OK;
 }
 
 }  // namespace
 
 extern "C" size_t spk_kwta_workspace_size(int B, int C, int H, int W) {
-    KwtaGeom g;
-    if (kwta_geom(B, 1, C, H, W, 1, 0, g) != SPK_OK) return 0;
-    KwtaSmall sm;
-    const int ntiles = kwta_small(B, 1, C, H, W, 1, 0, sm) ? sm.ntiles : g.ntiles;
-    size_t need = (size_t)B * ntiles * sizeof(uint64_t);
+    if (kwta_check(B, 1, C, H, W, 1, 0) != SPK_OK) return 0;
+    const KwtaUnits u = kwta_units(B, 1, C, H, W, 1, 0);
+    size_t need = (size_t)B * u.units * sizeof(uint64_t);
     if (B < TOPK_PRE_B && (int64_t)H * W <= TOPK_PRE_HW)  // the workgroup splits' lists (any k up to TOPK_MAX_K)
         need = std::max(need, (size_t)B * TOPK_PRE_NS * H * W * TOPK_MAX_K * sizeof(uint64_t));
     return spk::align_up(need, 256);
@@ -860,8 +700,7 @@ extern "C" size_t spk_kwta_workspace_size(int B, int C, int H, int W) {
 extern "C" int spk_kwta(const uint8_t *t_first, const float *v_first, int B, int T, int C, int H, int W, int k,
                         int radius, int32_t *winners, int32_t *n_winners, void *workspace, size_t ws_bytes,
                         void *stream) {
-    KwtaGeom g;
-    int rc = kwta_geom(B, T, C, H, W, k, radius, g);
+    int rc = kwta_check(B, T, C, H, W, k, radius);
     if (rc != SPK_OK) return rc;
     if (B == 0) return spk::ok();
     SPK_REQUIRE(t_first && v_first && winners && n_winners, SPK_E_ARG,
@@ -870,30 +709,23 @@ extern "C" int spk_kwta(const uint8_t *t_first, const float *v_first, int B, int
     SPK_REQUIRE(workspace && ws_bytes >= need, SPK_E_WORKSPACE, "spk_kwta: workspace of %zu bytes < %zu required",
                 ws_bytes, need);
     hipStream_t st = spk::as_stream(stream);
-    uint64_t *tilekey = static_cast<uint64_t *>(workspace);
     KwtaTopk tk;
     if (kwta_topk(B, T, C, H, W, k, radius, tk)) {
         tk.lg = static_cast<uint64_t *>(workspace);
         dispatch_topk(tk, t_first, v_first, winners, n_winners, st);
         return spk::check_launch("spk_kwta");
     }
-    KwtaSmall sm;
-    if (kwta_small(B, T, C, H, W, k, radius, sm)) {
-        const int64_t threads = (int64_t)B * sm.ntiles * 4;
-        const int vec = (sm.HW % 4) == 0 && ((uintptr_t)t_first & 3) == 0 && ((uintptr_t)v_first & 15) == 0;
-        hipLaunchKernelGGL(k_kwta_tiles16, dim3((unsigned)std::min<int64_t>(spk::ceil_div(threads, 256), 8192)),
-                           dim3(256), 0, st, t_first,
-                           v_first, sm, vec, tilekey);
-        const size_t lds = (size_t)sm.ntiles * (sizeof(uint64_t) + sizeof(uint16_t)) + (size_t)(sm.HW + 31) / 32 * 4;
-        hipLaunchKernelGGL(k_kwta_select_small, dim3(B), dim3(SMALL_THREADS), lds, st, t_first, v_first, sm, vec,
-                           tilekey, winners, n_winners);
-        return spk::check_launch("spk_kwta");
-    }
-    const int64_t threads = (int64_t)B * g.ntiles * g.G;
-    hipLaunchKernelGGL(k_kwta_tiles, dim3((unsigned)spk::ceil_div(threads, 256)), dim3(256), 0, st, t_first, v_first,
-                       g, tilekey);
-    const size_t lds = (size_t)g.ntiles * (sizeof(uint64_t) + sizeof(int)) + ((size_t)H * W + 31) / 32 * 4;
-    hipLaunchKernelGGL(k_kwta_select, dim3(B), dim3(SEL_THREADS), lds, st, t_first, v_first, g, tilekey, winners,
-                       n_winners);
+    KwtaUnits g = kwta_units(B, T, C, H, W, k, radius);
+    g.ukey = static_cast<uint64_t *>(workspace);
+    g.vec = g.L == 4 && g.HW % 4 == 0 && ((uintptr_t)t_first & 3) == 0 && ((uintptr_t)v_first & 15) == 0;
+    const int64_t blocks = (int64_t)B * ((g.units + 3) / 4);
+    SPK_REQUIRE(blocks < (1LL << 31), SPK_E_RANGE, "spk_kwta: batch too large");
+    hipLaunchKernelGGL(k_kwta_units, dim3((unsigned)blocks), dim3(256), 0, st, t_first, v_first, g);
+    const int nt = (int)std::min<int64_t>(UN_THREADS, spk::align_up((size_t)g.units, 64));
+    const size_t lds = (size_t)(g.HW + 31) / 32 * 4;
+    if (g.L == 4)
+        hipLaunchKernelGGL(k_kwta_rounds<4>, dim3(B), dim3(nt), lds, st, t_first, v_first, g, winners, n_winners);
+    else
+        hipLaunchKernelGGL(k_kwta_rounds<1>, dim3(B), dim3(nt), lds, st, t_first, v_first, g, winners, n_winners);
     return spk::check_launch("spk_kwta");
 }

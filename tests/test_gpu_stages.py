@@ -368,8 +368,8 @@ def test_pool_potentials_parity(case):
 # ---------------------------------------------------------------- kWTA
 # (B, T, C, H, W, k, radius).  Per-position top-k path: the first five, the
 # 1x1 and 1x9 maps, (300 maps of 10x10: feature split with the stash) and
-# (k = 16); 16-position tiles: (40x300 maps), (k = 20 > 16) and (k = 16 with
-# lists beyond LDS); row tiles: test_kwta_large_tiles.
+# (k = 16); units: (40x300 maps), (k = 20 > 16) and (k = 16 with lists beyond
+# LDS), KWTA_UNIT_CASES and test_kwta_large_tiles.
 KWTA_CASES = [(4, 15, 30, 28, 28, 5, 3), (3, 15, 250, 14, 14, 8, 1), (6, 15, 200, 4, 4, 1, 0),
               (2, 30, 20, 10, 25, 1, 5), (3, 4, 3, 5, 7, 12, 1), (2, 15, 5, 40, 300, 6, 2),
               (3, 15, 40, 1, 1, 4, 0), (2, 15, 7, 1, 9, 3, 1), (2, 15, 300, 10, 10, 8, 2),
@@ -416,6 +416,35 @@ def test_kwta_unaligned_inputs(case):
     rw, rn = orc.kwta(tf, vf, T, k, r)
     assert_equal(host(nw), rn, "n_winners")
     assert_equal(host(win), rw, "winners")
+
+
+# Units of 64 positions (below 4096 of them) or 256 (aligned or not) times 1 to 4096 maps
+KWTA_UNIT_CASES = [(1, 15, 4096, 1, 1, 40, 0), (2, 255, 300, 8, 8, 32, 2), (2, 15, 70, 13, 5, 17, 1),
+                   (3, 15, 5, 63, 65, 20, 3), (2, 15, 9, 64, 64, 20, 90), (1, 15, 40, 65, 64, 33, 5),
+                   (1, 20, 3, 256, 256, 3, 4), (2, 15, 600, 17, 40, 32, 2)]
+
+
+@pytest.mark.parametrize("case", KWTA_UNIT_CASES)
+@pytest.mark.parametrize("kind", ["ties", "shared", "dominated"])
+def test_kwta_units(case, kind):
+    """Random keys with ties; features that see the same input (their maxima at the same places);
+    features of which each is the best almost everywhere until it is retired."""
+    B, T, C, H, W, k, r = case
+    tf, vf = kwta_inputs(C + W, B, T, C, H, W, True)
+    g = synth.rng(330 + C, 0)
+    if kind == "shared":
+        tf = np.broadcast_to(g.integers(0, T + 1, (B, 1, H, W)), (B, C, H, W)).astype(np.uint8)
+        vf = (g.normal(40, 4, (B, 1, H, W)) + g.normal(0, 0.01, (B, C, H, W))).astype(np.float32)
+    elif kind == "dominated":
+        tf = np.zeros((B, C, H, W), np.uint8)
+        vf = (g.permutation(C)[None, :, None, None] * 100.0 + g.uniform(0, 40, (B, 1, H, W))).astype(np.float32)
+    vf[tf >= T] = 0
+    rw, rn = orc.kwta(tf, vf, T, k, r)
+    for put in (dev, dev_shifted):
+        win, nw = spk.spk_kwta(put(tf), put(vf), T, k, r)
+        sync()
+        assert_equal(host(nw), rn, "n_winners")
+        assert_equal(host(win), rw, "winners")
 
 
 def test_kwta_toy_t3_and_silent(golden):
