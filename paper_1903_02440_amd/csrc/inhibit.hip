@@ -4,139 +4,180 @@
 // only the neuron of the most salient feature -- the earliest spike, then the
 // highest potential -- may spike) and section "snn Module" (pooling applied
 // to a potentials tensor keeps the largest potential of each window).
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace {
 
-constexpr int PW_U = 8;  // features per block of loads in the pointwise inhibition
+constexpr int PW_THREADS = 512;
+constexpr int PW_LOC = 1024;    // locations of a workgroup at most
+constexpr int PW_SPLITS = 32;   // threads per 4 locations in the scan at most
+constexpr int PW_U = 8;         // features per block of loads in the scan
 
-// One thread per location of one image (VEC: per 4 consecutive locations,
-// with 4-byte / 16-byte accesses; the map size is then a multiple of 4): the
-// winner over the C features (the kWTA order: earlier spike, then larger
-// potential, then lower feature index), then every feature's surviving
-// first-spike time and potential, and, when asked, the survivors' Eq.1 wave
-// and the masked potentials.  All C features of the locations are read before
-// any is written, so the first-spike outputs may alias the inputs.
-// Consecutive threads take consecutive locations, so every per-feature
-// access of a wave is contiguous.
-template <bool VEC>
-__global__ __launch_bounds__(256) void k_pointwise(const uint8_t *tf, const float *vf, int64_t B, int T, int C,
-                                                   int64_t HW, uint8_t *out_t, float *out_v, uint8_t *wave,
-                                                   float *pot) {
-    constexpr int L = VEC ? 4 : 1;
-    const int64_t per_img = HW / L;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= B * per_img) return;
-    const int64_t b = q / per_img, p = (q - b * per_img) * L;
-    const int64_t base = b * C * HW + p;
-    int best[L], bt[L];
-    float bv[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-        best[j] = -1;
-        bt[j] = T;
-        bv[j] = 0.0f;
+// 4 values at any alignment, as one access where the hardware allows it.
+struct __attribute__((packed, aligned(1))) Byte4u {
+    uint32_t w;
+};
+struct __attribute__((packed, aligned(4))) Float4u {
+    float v[4];
+};
+
+// Grid: (part, run of up to PW_LOC locations, image).  The workgroup first finds
+// the winner of each of its locations over the C features (the kWTA order:
+// earlier spike, then larger potential, then lower feature index), 4 locations
+// and every n-th feature per thread, the threads' findings joined in LDS.  Then
+// it writes its part of the (feature, 4 locations) items: the surviving
+// first-spike time and potential, and, when asked, the survivors' Eq.1 wave and
+// zeros over the potentials of every feature that is no winner.  Nearly all of
+// that is constant, so nothing is read again.  All inputs of the locations are
+// read before any output is written and the parts of a run are only more than
+// one when the outputs are not the inputs, so the first-spike outputs may alias
+// the inputs.
+// Bound by the writes (5 (1 + T) bytes a neuron with wave and potentials).  With
+// one thread per 4 locations doing all of it (the form before), 200 images of 250
+// maps of 14x14 kept 39 workgroups busy and read the potentials: 1444 us; now
+// 245 us (833 MB, 3.4 TB/s).  256 or 1024 threads per workgroup 265 and 280 us;
+// items in the inner loop, steps in the outer one 280 us.
+//
+// A potential that is no number never replaces another one, and is replaced by
+// none at the same step when it comes first: the scan keeps the first feature of
+// the earliest step and whether its potential is a number beside the best one.
+struct PwBest {
+    int t, c, first;  // step, best feature (-1: none), 2 * first feature + [its potential is no number]
+    float v;
+};
+__device__ __forceinline__ void pw_join(PwBest &a, int t, int c, int first, float v) {
+    if (first < 0 || t > a.t) return;
+    if (t < a.t || a.first < 0) {
+        a = PwBest{t, c, first, v};
+        return;
     }
-    // features in blocks of PW_U, every load of a block issued before the
-    // first is used (clamped feature indices keep them unconditional), in
-    // increasing feature order so that strict comparisons keep the lower index
-    for (int c0 = 0; c0 < C; c0 += PW_U) {
-        uint32_t tw[PW_U];
-        float4 vw[PW_U];
+    a.first = min(a.first, first);
+    if (c >= 0 && (a.c < 0 || v > a.v || (v == a.v && c < a.c))) {
+        a.c = c;
+        a.v = v;
+    }
+}
+
+__global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, const float *vf, int T, int C, int HW,
+                                                          int nrun, int parts, uint8_t *out_t, float *out_v,
+                                                          uint8_t *wave, float *pot) {
+    extern __shared__ uint4 pwsm[];  // [splits][4 nq] findings
+    __shared__ __align__(16) int bc[PW_LOC];
+    __shared__ float bv[PW_LOC];
+    __shared__ uint8_t bt[PW_LOC];
+    const int tid = threadIdx.x;
+    const int part = blockIdx.x % parts, run = (blockIdx.x / parts) % nrun;
+    const int64_t b = blockIdx.x / parts / nrun;
+    const int p0 = run * PW_LOC, n = min(PW_LOC, HW - p0), nq = (n + 3) / 4;
+    const int splits = min(min(PW_SPLITS, PW_THREADS / nq), C);
+    const int64_t plane = (int64_t)C * HW, base = b * plane + p0;
+    PwBest *found = reinterpret_cast<PwBest *>(pwsm);
+    if (tid < nq * splits) {
+        const int sp = tid / nq, q = tid - sp * nq, nj = min(4, n - 4 * q);
+        PwBest best[4];
 #pragma unroll
-        for (int u = 0; u < PW_U; ++u) {
-            const int64_t o = base + (int64_t)min(c0 + u, C - 1) * HW;
-            if (VEC) {
-                tw[u] = *reinterpret_cast<const uint32_t *>(tf + o);
-                vw[u] = *reinterpret_cast<const float4 *>(vf + o);
-            } else {
-                tw[u] = tf[o];
-                vw[u].x = vf[o];
-            }
-        }
+        for (int j = 0; j < 4; ++j) best[j] = PwBest{T, -1, -1, 0.0f};
+        for (int c0 = sp; c0 < C; c0 += PW_U * splits) {
+            uint32_t tw[PW_U];
+            Float4u vw[PW_U];
+            if (nj == 4) {
 #pragma unroll
-        for (int u = 0; u < PW_U; ++u) {
-            const int c = c0 + u;
-            if (c >= C) break;
-            int t[L];
-            float v[L];
-            t[0] = tw[u] & 255u;
-            v[0] = vw[u].x;
-            if (VEC) {
-                t[L > 1 ? 1 : 0] = (tw[u] >> 8) & 255u;
-                t[L > 2 ? 2 : 0] = (tw[u] >> 16) & 255u;
-                t[L > 3 ? 3 : 0] = tw[u] >> 24;
-                v[L > 1 ? 1 : 0] = vw[u].y; v[L > 2 ? 2 : 0] = vw[u].z; v[L > 3 ? 3 : 0] = vw[u].w;
-            }
-#pragma unroll
-            for (int j = 0; j < L; ++j)
-                if (t[j] < T && (best[j] < 0 || t[j] < bt[j] || (t[j] == bt[j] && v[j] > bv[j]))) {
-                    best[j] = c;
-                    bt[j] = t[j];
-                    bv[j] = v[j];
+                for (int u = 0; u < PW_U; ++u) {  // (clamped: unconditional loads, all in flight)
+                    const int64_t o = base + (int64_t)min(c0 + u * splits, C - 1) * HW + 4 * q;
+                    tw[u] = reinterpret_cast<const Byte4u *>(tf + o)->w;
+                    vw[u] = *reinterpret_cast<const Float4u *>(vf + o);
                 }
-        }
-    }
-    // the surviving first-spike times of feature c, 4 to a word
-    auto word = [&](int c) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int j = 0; j < L; ++j) w |= (uint32_t)(c == best[j] ? bt[j] : T) << (8 * j);
-        return w;
-    };
-    for (int c = 0; c < C; ++c) {
-        if (VEC) {
-            *reinterpret_cast<uint32_t *>(out_t + base + c * HW) = word(c);
-            *reinterpret_cast<float4 *>(out_v + base + c * HW) =
-                float4{c == best[0] ? bv[0] : 0.0f, c == best[L > 1 ? 1 : 0] ? bv[L > 1 ? 1 : 0] : 0.0f,
-                       c == best[L > 2 ? 2 : 0] ? bv[L > 2 ? 2 : 0] : 0.0f,
-                       c == best[L > 3 ? 3 : 0] ? bv[L > 3 ? 3 : 0] : 0.0f};
-        } else {
-            out_t[base + c * HW] = (uint8_t)(c == best[0] ? bt[0] : T);
-            out_v[base + c * HW] = c == best[0] ? bv[0] : 0.0f;
-        }
-    }
-    const int64_t plane = (int64_t)C * HW;
-    if (wave)  // feature by feature: its surviving times once, then its T steps
-        for (int c = 0; c < C; ++c) {
-            uint8_t *w = wave + b * T * plane + (int64_t)c * HW + p;
-            if (VEC) {
-                const uint32_t wc = word(c);
-                for (int t = 0; t < T; ++t) *reinterpret_cast<uint32_t *>(w + t * plane) = spk::spikes4(wc, t, T);
             } else {
-                const int tc = c == best[0] ? bt[0] : T;
-                for (int t = 0; t < T; ++t) w[t * plane] = (uint8_t)(t >= tc);
-            }
-        }
-    if (pot)
-        for (int t = 0; t < T; ++t) {
-            float *pp = pot + (b * T + t) * plane + p;
-            if constexpr (VEC) {
-                // blocks of PW_U features: the loads first (clamped), then the masked stores
-                for (int c0 = 0; c0 < C; c0 += PW_U) {
-                    float4 xw[PW_U];
 #pragma unroll
-                    for (int u = 0; u < PW_U; ++u)
-                        xw[u] = *reinterpret_cast<const float4 *>(pp + (int64_t)min(c0 + u, C - 1) * HW);
+                for (int u = 0; u < PW_U; ++u) {
+                    const int64_t o = base + (int64_t)min(c0 + u * splits, C - 1) * HW + 4 * q;
+                    tw[u] = 0;
 #pragma unroll
-                    for (int u = 0; u < PW_U; ++u) {
-                        const int c = c0 + u;
-                        if (c >= C) break;
-                        if (c == best[0] && c == best[1] && c == best[2] && c == best[3])
-                            continue;  // the feature survives at all four locations
-                        float4 x = xw[u];
-                        if (c != best[0]) x.x = 0.0f;
-                        if (c != best[1]) x.y = 0.0f;
-                        if (c != best[2]) x.z = 0.0f;
-                        if (c != best[3]) x.w = 0.0f;
-                        *reinterpret_cast<float4 *>(pp + (int64_t)c * HW) = x;
+                    for (int j = 0; j < 4; ++j) {
+                        tw[u] |= (uint32_t)tf[o + min(j, nj - 1)] << (8 * j);
+                        vw[u].v[j] = vf[o + min(j, nj - 1)];
                     }
                 }
-            } else {
-                for (int c = 0; c < C; ++c)
-                    if (c != best[0]) pp[c * HW] = 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < PW_U; ++u) {
+                const int c = c0 + u * splits;
+                if (c >= C) break;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int t = (int)((tw[u] >> (8 * j)) & 255u);
+                    const float v = vw[u].v[j];
+                    if (t < T) pw_join(best[j], t, v == v ? c : -1, 2 * c + (v == v ? 0 : 1), v);
+                }
             }
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) found[sp * 4 * nq + 4 * q + j] = best[j];
+    }
+    __syncthreads();
+    for (int p = tid; p < 4 * nq; p += PW_THREADS) {
+        PwBest a = found[p];
+        for (int sp = 1; sp < splits; ++sp) {
+            const PwBest o = found[sp * 4 * nq + p];
+            pw_join(a, o.t, o.c, o.first, o.v);
+        }
+        const bool nan_first = a.first >= 0 && (a.first & 1);
+        bc[p] = p < n ? (nan_first ? a.first >> 1 : a.c) : -1;
+        bt[p] = (uint8_t)a.t;
+        bv[p] = nan_first ? __int_as_float(0x7FC00000) : a.v;
+    }
+    __syncthreads();
+    const int64_t items = (int64_t)C * nq, i1 = items * (part + 1) / parts;
+    for (int64_t i = items * part / parts + tid; i < i1; i += PW_THREADS) {
+        const int c = (int)(i / nq), q = (int)(i - (int64_t)c * nq), nj = min(4, n - 4 * q);
+        const int4 w4 = *reinterpret_cast<const int4 *>(bc + 4 * q);
+        const bool k[4] = {w4.x == c, w4.y == c, w4.z == c, w4.w == c};
+        const int64_t o = base + (int64_t)c * HW + 4 * q, ow = b * T * plane + p0 + (int64_t)c * HW + 4 * q;
+        uint32_t tw = 0;
+        Float4u v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            tw |= (uint32_t)(k[j] ? (int)bt[4 * q + j] : T) << (8 * j);
+            v.v[j] = k[j] ? bv[4 * q + j] : 0.0f;
+        }
+        const bool any = k[0] || k[1] || k[2] || k[3];
+        if (nj == 4) {
+            reinterpret_cast<Byte4u *>(out_t + o)->w = tw;
+            *reinterpret_cast<Float4u *>(out_v + o) = v;
+            if (wave) {
+                if (any)
+                    for (int t = 0; t < T; ++t)
+                        reinterpret_cast<Byte4u *>(wave + ow + t * plane)->w = spk::spikes4(tw, t, T);
+                else
+                    for (int t = 0; t < T; ++t) reinterpret_cast<Byte4u *>(wave + ow + t * plane)->w = 0;
+            }
+            if (pot) {
+                if (any)
+                    for (int t = 0; t < T; ++t)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            if (!k[j]) pot[ow + t * plane + j] = 0.0f;
+                        }
+                else
+                    for (int t = 0; t < T; ++t)
+                        *reinterpret_cast<Float4u *>(pot + ow + t * plane) = Float4u{{0.0f, 0.0f, 0.0f, 0.0f}};
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (j >= nj) continue;
+                const int tj = (int)((tw >> (8 * j)) & 255u);
+                out_t[o + j] = (uint8_t)tj;
+                out_v[o + j] = v.v[j];
+                if (wave)
+                    for (int t = 0; t < T; ++t) wave[ow + t * plane + j] = (uint8_t)(t >= tj);
+                if (pot && !k[j])
+                    for (int t = 0; t < T; ++t) pot[ow + t * plane + j] = 0.0f;
+            }
+        }
+    }
 }
 
 // One thread per output value: the maximum over the window of the zero-padded
@@ -183,6 +224,24 @@ __global__ __launch_bounds__(256) void k_pool_potentials_2x2(const float *__rest
         float2{win(a.x, a.y, c.x, c.y), win(a.z, a.w, c.z, c.w)};
 }
 
+// The same for even widths (8-byte aligned rows): one output per thread, from
+// one 8-byte load of each of its two rows.  Single loads reach every other
+// column of two rows at a time: 200 images of 250 maps of 14x14, T = 15, took
+// 189 us; now 178 us (4.1 TB/s).
+__global__ __launch_bounds__(256) void k_pool_potentials_2x2_even(const float *__restrict__ pot, uint32_t total, int H,
+                                                                  int W, int Ho, int Wo, float *__restrict__ out) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= total) return;
+    const uint32_t hw = (uint32_t)(Ho * Wo), pl = i / hw, r = i - pl * hw, yo = r / (uint32_t)Wo, xo = r - yo * Wo;
+    const float *src = pot + (size_t)pl * H * W + (size_t)(2 * yo) * W + 2 * xo;
+    const float2 a = *reinterpret_cast<const float2 *>(src), c = *reinterpret_cast<const float2 *>(src + W);
+    float m = a.x;
+    if (a.y > m) m = a.y;
+    if (c.x > m) m = c.x;
+    if (c.y > m) m = c.y;
+    out[i] = m;
+}
+
 }  // namespace
 
 extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_first, int B, int T, int C, int H,
@@ -195,16 +254,24 @@ extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_f
                 "spk_pointwise_inhibition: t_first, v_first, out_t_first and out_v_first are required");
     const int64_t HW = (int64_t)H * W, total = (int64_t)B * HW;
     SPK_REQUIRE(spk::ceil_div(total, 256) < (1LL << 31), SPK_E_RANGE, "spk_pointwise_inhibition: too large");
-    auto al = [](const void *q, uintptr_t a) { return ((uintptr_t)q & (a - 1)) == 0; };
-    const bool vec = HW % 4 == 0 && al(t_first, 4) && al(out_t_first, 4) && al(out_wave, 4) && al(v_first, 16) &&
-                     al(out_v_first, 16) && al(potentials, 16);
+    SPK_REQUIRE(HW < (1LL << 31) && (int64_t)C * HW < (1LL << 40), SPK_E_RANGE, "spk_pointwise_inhibition: too large");
+    const int64_t nrun = spk::ceil_div(HW, PW_LOC);
+    // more workgroups per run where the runs are few (each scans the run's inputs for
+    // itself: 5 bytes a neuron, from L2 after the first), unless outputs are inputs
+    const int64_t N = (int64_t)B * C * HW;
+    auto overlap = [](const void *a, int64_t na, const void *b, int64_t nb) {
+        const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+        return x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
+    };
+    const bool alias = overlap(out_t_first, N, t_first, N) || overlap(out_t_first, N, v_first, 4 * N) ||
+                       overlap(out_v_first, 4 * N, t_first, N) || overlap(out_v_first, 4 * N, v_first, 4 * N);
+    const int64_t per_run = spk::ceil_div((int64_t)C * spk::ceil_div(std::min<int64_t>(HW, PW_LOC), 4), PW_THREADS);
+    const int64_t parts = alias ? 1 : std::max<int64_t>(1, std::min<int64_t>({1024 / (B * nrun), 8, per_run}));
+    SPK_REQUIRE(B * nrun * parts < (1LL << 31), SPK_E_RANGE, "spk_pointwise_inhibition: too large");
     hipStream_t st = spk::as_stream(stream);
-    if (vec)
-        hipLaunchKernelGGL(k_pointwise<true>, dim3((unsigned)spk::ceil_div(total / 4, 256)), dim3(256), 0, st, t_first,
-                           v_first, (int64_t)B, T, C, HW, out_t_first, out_v_first, out_wave, potentials);
-    else
-        hipLaunchKernelGGL(k_pointwise<false>, dim3((unsigned)spk::ceil_div(total, 256)), dim3(256), 0, st, t_first,
-                           v_first, (int64_t)B, T, C, HW, out_t_first, out_v_first, out_wave, potentials);
+    hipLaunchKernelGGL(k_pointwise, dim3((unsigned)(B * nrun * parts)), dim3(PW_THREADS),
+                       (size_t)PW_THREADS * 4 * sizeof(PwBest), st, t_first, v_first, T, C, (int)HW, (int)nrun,
+                       (int)parts, out_t_first, out_v_first, out_wave, potentials);
     return spk::check_launch("spk_pointwise_inhibition");
 }
 
@@ -226,6 +293,12 @@ extern "C" int spk_pool_potentials(const float *potentials, int B, int T, int C,
         const int64_t pairs = total / 2;
         hipLaunchKernelGGL(k_pool_potentials_2x2, dim3((unsigned)spk::ceil_div(pairs, 256)), dim3(256), 0,
                            spk::as_stream(stream), potentials, (uint32_t)pairs, H, W, Ho, Wo, out);
+        return spk::check_launch("spk_pool_potentials");
+    }
+    if (kernel == 2 && stride == 2 && pad == 0 && W % 2 == 0 && ((uintptr_t)potentials & 7) == 0 &&
+        total < (1LL << 32) - 256) {
+        hipLaunchKernelGGL(k_pool_potentials_2x2_even, dim3((unsigned)spk::ceil_div(total, 256)), dim3(256), 0,
+                           spk::as_stream(stream), potentials, (uint32_t)total, H, W, Ho, Wo, out);
         return spk::check_launch("spk_pool_potentials");
     }
     hipLaunchKernelGGL(k_pool_potentials, dim3((unsigned)spk::ceil_div(total, 256)), dim3(256), 0,

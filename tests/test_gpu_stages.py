@@ -348,12 +348,42 @@ def test_pointwise_inhibition_parity(case):
     assert_equal(host(iv), rv, "v_first in place")
 
 
+# Runs of up to 1024 locations: ragged quads, a run of the last few, one location, T > 127, many
+# parts per run; unaligned tensors; potentials that are no numbers or infinite
+@pytest.mark.parametrize("case", [(1, 6, 9, 40, 41), (2, 130, 3, 33, 32), (3, 15, 1, 1, 1), (1, 20, 260, 32, 32),
+                                  (2, 7, 5, 27, 38)])
+@pytest.mark.parametrize("put", [dev, dev_shifted])
+def test_pointwise_inhibition_runs(case, put):
+    B, T, C, H, W = case
+    g = synth.rng(720 + C + H, 0)
+    tf = synth.times_uniform_or_silent(g, (B, C, H, W), T, 0.5)
+    tf[:, :, 0] = g.integers(0, 2, (B, C, W))  # equal times: the potentials decide
+    vf = (g.integers(0, 6, (B, C, H, W)) * 0.5).astype(np.float32)
+    vf[g.random(vf.shape) < 0.2] = np.nan
+    vf[g.random(vf.shape) < 0.1] = -np.inf
+    vf[g.random(vf.shape) < 0.05] = np.inf
+    vf[tf >= T] = 0
+    pot = g.normal(0, 3, (B, T, C, H, W)).astype(np.float32)
+    rt, rv, rp = orc.pointwise_inhibition(tf, vf, T, pot)
+    gp, it, iv = put(pot), put(tf), put(vf)
+    ot, ov, ow = spk.spk_pointwise_inhibition(it, iv, T, out_wave=None, potentials=gp)
+    spk.spk_pointwise_inhibition(it, iv, T, out_t_first=it, out_v_first=iv)
+    sync()
+    for what, t, v in (("", ot, ov), (" in place", it, iv)):
+        assert_equal(host(t), rt, "t_first" + what)
+        assert_equal(np.isnan(host(v)), np.isnan(rv), "v_first not a number" + what)
+        assert_equal(np.nan_to_num(host(v), nan=-1.0), np.nan_to_num(rv, nan=-1.0), "v_first" + what)
+    assert_equal(host(ow), orc.expand_wave(rt, T), "wave")
+    assert_equal(host(gp), rp, "masked potentials")
+
+
 # 2x2 windows of stride 2 on widths that are multiples of 4 take 16-byte loads of
 # two rows (the 28x28 map; an odd height, whose last row no window covers); the
 # rest one output per thread
 @pytest.mark.parametrize("case", [(2, 15, 30, 28, 28, 2, 2, 0), (2, 15, 250, 14, 14, 3, 3, 0),
                                   (1, 5, 4, 9, 11, 3, 2, 1), (1, 3, 2, 7, 7, 4, 3, 2), (2, 4, 3, 5, 6, 1, 1, 0),
-                                  (2, 3, 5, 9, 12, 2, 2, 0), (1, 2, 3, 6, 10, 2, 2, 0)])
+                                  (2, 3, 5, 9, 12, 2, 2, 0), (1, 2, 3, 6, 10, 2, 2, 0),
+                                  (2, 3, 5, 7, 14, 2, 2, 0), (1, 2, 3, 2, 2, 2, 2, 0)])  # (even widths: 8-byte loads)
 def test_pool_potentials_parity(case):
     B, T, C, H, W, P, R, D = case
     g = synth.rng(800 + P + C, 0)
