@@ -519,14 +519,18 @@ __device__ __forceinline__ void neg_times(uint32_t w, uint32_t &lo, uint32_t &hi
 }
 
 // Spike operand of 8 taps at step t: clamp((1025 + t) - (1024 + tp)) per tap,
-// fp16 1.0 / 0 (as bf16: 2^-7 / 0).
+// fp16 1.0 / 0 (as bf16: 2^-7 / 0).  Each pair is one v_pk_add_f16 with clamp,
+// written so that the compiler selects it: as inline assembly it hid from the
+// compiler that a register an MFMA was still reading as its addend, or writing,
+// was overwritten, and the wait states that takes were left out.
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t spike_pair(uint32_t ct, uint32_t xn) {
+    const half2v s = __builtin_bit_cast(half2v, ct) + __builtin_bit_cast(half2v, xn);
+    const half2v zero = {(_Float16)0, (_Float16)0}, one = {(_Float16)1, (_Float16)1};
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_elementwise_max(s, zero), one));
+}
 __device__ __forceinline__ u4 spike_operand(const uint32_t (&xn)[4], uint32_t ct) {
-    u4 a;
-    asm("v_pk_add_f16 %0, %1, %2 clamp" : "=v"(a.x) : "v"(ct), "v"(xn[0]));
-    asm("v_pk_add_f16 %0, %1, %2 clamp" : "=v"(a.y) : "v"(ct), "v"(xn[1]));
-    asm("v_pk_add_f16 %0, %1, %2 clamp" : "=v"(a.z) : "v"(ct), "v"(xn[2]));
-    asm("v_pk_add_f16 %0, %1, %2 clamp" : "=v"(a.w) : "v"(ct), "v"(xn[3]));
-    return a;
+    return u4{spike_pair(ct, xn[0]), spike_pair(ct, xn[1]), spike_pair(ct, xn[2]), spike_pair(ct, xn[3])};
 }
 
 // fp16 (1025 + t) in both halves (t <= 1022)
