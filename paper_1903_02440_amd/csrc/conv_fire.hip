@@ -57,6 +57,14 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
+// 4 elements at any alignment, as one access where the hardware allows it
+struct __attribute__((packed, aligned(4))) PackedF4 {
+    float v[4];
+};
+struct __attribute__((packed, aligned(1))) PackedU4 {
+    uint32_t w;
+};
+
 constexpr int NTILE_ALIGN = 4;  // the N tiles (16 features) are padded to a multiple of this
 
 // 16 bytes per lane from global memory into LDS at byte offset m0 + 16*lane.
@@ -1153,6 +1161,351 @@ __global__ __launch_bounds__(FIN_THREADS, 1) void k_conv_fire_fin(
     }
 }
 
+// ------------------------------------------------------------------ 3a'. finite threshold, streamed weights
+// Layers whose weight fragments do not fit in LDS beside the staging area of
+// k_conv_fire_fin (a pair of 16-feature tiles of more than about 16 K-steps; the
+// smallest that do not fit run as fast here, those of 13 K-steps 20 % slower).
+// A workgroup of TG groups of 4 waves makes NP = 64 * MT positions of the
+// flattened (image, position) space times 16 * NTL features for all steps; a wave
+// holds MT position tiles x NTL feature tiles x STR_TB steps of accumulators, the
+// groups of waves consecutive runs of STR_TB steps.  The fragments of KC K-steps
+// at a time go through two LDS buffers, shared by all waves: the transfers of the
+// next chunk are issued right after the barrier that hands over the current one
+// and are waited for at the next, a whole chunk of products later.  The rows of
+// the padded map that the positions see are in LDS for the whole run where they
+// fit (ALDS), else their words come from L2 one chunk ahead.  After a block of
+// steps the accumulators go through LDS, 32 features of a step at a time, so that
+// P and S leave as runs of NP positions; first spikes are written when they happen
+// (steps in order, one bit per neuron remembers them).
+// Bound by the matrix cores where K is large: the layer of 64 256x256 maps, 256
+// features of 5x5, T = 64 takes 5.0 ms (1.4 PFLOP/s in two 16-bit terms; a large
+// bf16 matrix product reaches 1.23 here), elsewhere by the latency of the staged
+// stores, which other waves cover.  With each wave reading the fragments from L2
+// for itself (8 times the traffic, one K-step ahead) it took 12.5 ms, and 31
+// 65x43 maps of 13 channels, 70 features of 7x7, stride 2: 399 us, now 202.
+constexpr int STR_TB = 3;
+__host__ __device__ constexpr int str_kc(int MT, int NTL) { return MT * NTL >= 8 ? 2 : 4; }
+__host__ __device__ constexpr int str_chunk_u4(int MT, int NTL) { return str_kc(MT, NTL) * NTL * NT * 64; }
+__host__ __device__ constexpr int str_stage(int MT) { return 32 * (64 * MT + 4); }  // floats
+
+constexpr size_t str_lds(int MT, int NTL, int ksteps, size_t rows_bytes) {
+    return 2 * (size_t)str_chunk_u4(MT, NTL) * 16 + (size_t)str_stage(MT) * 4 + (size_t)ksteps * 4 * sizeof(int2) +
+           rows_bytes;
+}
+
+// A lane's spike words, waited for: the compiler takes them as defined here, so
+// it does not wait again where they are used (behind transfers it cannot count).
+template <int KC, int MT>
+__device__ __forceinline__ void str_landed(uint32_t (&w)[KC][MT][2]) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < KC; ++k)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) asm volatile("" : "+v"(w[k][i][0]), "+v"(w[k][i][1]));
+}
+
+template <int MT, int NTL, int TG, bool ALDS>
+__global__ __launch_bounds__(256 * TG, 2) void k_conv_fire_str(
+    const uint8_t *__restrict__ tpad, const uint4 *__restrict__ frag, const int2 *__restrict__ koff2, ConvGeom g,
+    int n_fg, int n_chunks, const float *__restrict__ inv_scale, const int *__restrict__ wbf16, float *__restrict__ P,
+    uint8_t *__restrict__ S, uint8_t *__restrict__ TF, float *__restrict__ VF) {
+    constexpr int KC = str_kc(MT, NTL), CHUNK = str_chunk_u4(MT, NTL), NP = 64 * MT, SP = NP + 4;
+    constexpr int TB = STR_TB, THREADS = 256 * TG;
+    constexpr int GPW = KC * NTL * NT / (4 * TG);  // 1 KB transfers per wave and chunk
+    extern __shared__ uint4 lds[];
+    uint4 *ring = lds;                                               // [2][CHUNK]
+    float *stage = reinterpret_cast<float *>(ring + 2 * CHUNK);      // [32][SP]
+    int2 *koff_l = reinterpret_cast<int2 *>(stage + str_stage(MT));  // [ksteps][4]
+    // ALDS: the chunk's padded rows, channel-group major [row][CP/8][Wp][8 bytes] (CP == 4: [row][Wp][4])
+    uint32_t *arow = reinterpret_cast<uint32_t *>(koff_l + g.ksteps * 4);
+    const uint32_t ring_lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)ring;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wv = wave & 3, tg = wave >> 2;
+    const int gq = lane >> 4, c = lane & 15;
+    // an XCD (workgroup id mod 8) takes a run of position chunks, all feature groups of each
+    const int per_x = (n_chunks + 7) / 8, xc = blockIdx.x % 8, jx = blockIdx.x / 8;
+    const int chunk = xc * per_x + jx / n_fg, fg = jx % n_fg;
+    if (jx / n_fg >= per_x || chunk >= n_chunks) return;  // uniform
+    const float inv_s = *inv_scale;
+    const int kind = *wbf16;
+    const int npos = g.B * g.HoWo, p0 = chunk * NP, f0 = fg * NTL * 16, row_bytes = g.Wp * g.CP;
+    auto tpad_row = [&](int gp) {  // first padded row of a position's window
+        const int b = gp / g.HoWo, pos = gp - b * g.HoWo;
+        return b * g.Hp + pos / g.Wo * g.S;
+    };
+    const int row0 = tpad_row(p0);
+    if (ALDS) {
+        const int KK = g.K * g.K, cell = g.CP >= 8 ? 8 : 4;
+        for (int i = tid; i < g.ksteps * 4; i += THREADS) {
+            int2 o{0, 0};
+            if (g.CP >= 8) {
+                int kyx, ci0;
+                tap_of(g, i >> 2, i & 3, 0, kyx, ci0);
+                if (kyx < KK) o.x = (kyx / g.K) * row_bytes + (ci0 >> 3) * g.Wp * cell + (kyx % g.K) * cell;
+                o.y = o.x + 4;
+            } else {
+                o = koff_of(g, i);  // (cells of 4 bytes: the rows as they are)
+            }
+            koff_l[i] = o;
+        }
+        const int nw = (tpad_row(min(p0 + NP, npos) - 1) + g.K - row0) * row_bytes / 4;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(tpad + (int64_t)row0 * row_bytes);
+        const int rw = row_bytes / 4, gw = 2 * g.Wp, cw = g.CP / 4;
+        for (int d0 = tid; d0 < nw; d0 += 8 * THREADS) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int d = min(d0 + u * THREADS, nw - 1), rr = d / rw, rem = d - rr * rw;
+                const int cg = rem / gw, r2 = rem - cg * gw;
+                v[u] = src[g.CP >= 8 ? rr * rw + (r2 >> 1) * cw + cg * 2 + (r2 & 1) : d];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (d0 + u * THREADS < nw) arow[d0 + u * THREADS] = v[u];
+        }
+    } else {
+        for (int i = tid; i < g.ksteps * 4; i += THREADS) koff_l[i] = koff2[i];
+    }
+    uint32_t abase[MT];  // of the lane's window: in tpad, or in arow
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const int gp = min(p0 + (wv * MT + i) * 16 + c, npos - 1);  // rows past the end are computed, not stored
+        const int b = gp / g.HoWo, pos = gp - b * g.HoWo;
+        const int y = pos / g.Wo, x = (pos - y * g.Wo) * g.S;
+        abase[i] = ALDS ? (uint32_t)((b * g.Hp + y * g.S - row0) * row_bytes + x * (g.CP >= 8 ? 8 : 4))
+                        : (uint32_t)((((int64_t)b * g.Hp + y * g.S) * g.Wp + x) * g.CP);
+    }
+    // this thread's 4 positions of the stores (the same for all its features)
+    constexpr int PG = NP / 4, FSTEP = THREADS / PG < 32 ? THREADS / PG : 32, M = 32 / FSTEP;  // M features of 32
+    const int pg = tid % PG;
+    const int gp0 = p0 + 4 * pg, sb = min(gp0, npos - 1) / g.HoWo, spos = gp0 - sb * g.HoWo;
+    const int nq = tid < 32 * PG ? min(4, npos - gp0) : 0;  // valid positions (<= 0: none)
+    const bool quad = nq == 4 && spos + 3 < g.HoWo;
+    const int64_t fplane = (int64_t)g.Cout * g.HoWo;
+    const bool al = ((uintptr_t)P & 15) == 0 && ((uintptr_t)S & 3) == 0 && (g.HoWo & 3) == 0;
+    // element offsets of (image, feature f0 + fl0, step 0) and of its first-spike entry
+    const int64_t oP0 = (int64_t)sb * g.T * fplane + (int64_t)(f0 + tid / PG) * g.HoWo + spos;
+    const int64_t oF0 = (int64_t)sb * fplane + (int64_t)(f0 + tid / PG) * g.HoWo + spos;
+    const int nfl = g.Cout - f0 - tid / PG;    // features from this thread's first on
+    uint32_t fired = 0;  // bit (half * M + m) * 4 + q
+    const int nch = (g.ksteps + KC - 1) / KC;
+    __syncthreads();  // koff_l, arow
+
+    auto run = [&](auto kind_c) {
+        constexpr int KIND = decltype(kind_c)::value;
+        auto words = [&](int ch, uint32_t (&w)[KC][MT][2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < KC; ++k) {
+                const int ks = ch * KC + k;
+                const int2 o = koff_l[min(ks, g.ksteps - 1) * 4 + gq];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    if (ALDS) {
+                        const uint8_t *ar = reinterpret_cast<const uint8_t *>(arow) + abase[i];
+                        if (g.CP >= 8) {
+                            const uint2 v = *reinterpret_cast<const uint2 *>(ar + (uint32_t)o.x);
+                            w[k][i][0] = v.x;
+                            w[k][i][1] = v.y;
+                        } else {
+                            w[k][i][0] = *reinterpret_cast<const uint32_t *>(ar + (uint32_t)o.x);
+                            w[k][i][1] = *reinterpret_cast<const uint32_t *>(ar + (uint32_t)o.y);
+                        }
+                    } else if (g.CP >= 8) {
+                        const uint2 v = *reinterpret_cast<const uint2 *>(tpad + (abase[i] + (uint32_t)o.x));
+                        w[k][i][0] = v.x;
+                        w[k][i][1] = v.y;
+                    } else {
+                        w[k][i][0] = *reinterpret_cast<const uint32_t *>(tpad + (abase[i] + (uint32_t)o.x));
+                        w[k][i][1] = *reinterpret_cast<const uint32_t *>(tpad + (abase[i] + (uint32_t)o.y));
+                    }
+                }
+            }
+        };
+        auto fill = [&](int ch, int buf) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < GPW; ++u) {
+                const int grp = wave + 4 * TG * u, q = grp % NT, n = (grp / NT) % NTL, k = grp / (NT * NTL);
+                const uint4 *src =
+                    frag + (((int64_t)(fg * NTL + n) * g.ksteps + min(ch * KC + k, g.ksteps - 1)) * NT + q) * 64 + lane;
+                lds_dma16(src, __builtin_amdgcn_readfirstlane(ring_lds + (uint32_t)(buf * CHUNK + grp * 64) * 16u));
+            }
+        };
+        f4 acc[MT][NTL][TB];
+        auto products = [&](int ch, int buf, int tb0, const uint32_t (&w)[KC][MT][2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < KC; ++k) {
+                // K-steps past the last one: spikes that never happen (their fragments repeat the last's)
+                const bool in = ch * KC + k < g.ksteps;
+                const uint4 *fr = ring + buf * CHUNK + k * NTL * NT * 64 + lane;
+                uint4 bt[NTL][NT];
+#pragma unroll
+                for (int n = 0; n < NTL; ++n)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) bt[n][q] = fr[(n * NT + q) * 64];
+                uint32_t xn[MT][4];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    neg_times(in ? w[k][i][0] : 0xFFFFFFFFu, xn[i][0], xn[i][1]);
+                    neg_times(in ? w[k][i][1] : 0xFFFFFFFFu, xn[i][2], xn[i][3]);
+                }
+#pragma unroll
+                for (int t = 0; t < TB; ++t) {
+                    const uint32_t ct = step_const(tb0 + tg * TB + t);
+                    u4 a[MT];
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) a[i] = spike_operand(xn[i], ct);
+#pragma unroll
+                    for (int q = 0; q < NT; ++q)
+#pragma unroll
+                        for (int i = 0; i < MT; ++i)
+#pragma unroll
+                            for (int n = 0; n < NTL; ++n) acc[i][n][t] = mfma<KIND>(a[i], bt[n][q], acc[i][n][t]);
+                }
+            }
+        };
+        // the staged 32 features of step t: fire and store (half: which 32 of the group)
+        auto store = [&](int t, int half) __attribute__((always_inline)) {
+            if (nq <= 0) return;
+            int64_t oP = oP0, oF = oF0;
+            asm volatile("" : "+v"(oP), "+v"(oF));  // the addresses are formed here, not kept through the K loop
+            const float *st = stage + tid / PG * SP + 4 * pg;
+            const int64_t ut = (int64_t)t * fplane;
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const int64_t uf = (int64_t)(half * 32 + m * FSTEP) * g.HoWo;  // (uniform)
+                if (half * 32 + m * FSTEP >= nfl) continue;
+                const f4 v = *reinterpret_cast<const f4 *>(st + m * FSTEP * SP);
+                const int sh = (half * M + m) * 4;
+                uint32_t fire = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) fire |= v[q] >= g.thr ? 1u << q : 0u;
+                const uint32_t fresh = fire & ~(fired >> sh);
+                fired |= fire << sh;
+                if (quad) {
+                    const uint32_t sp = (fire * 0x00204081u) & 0x01010101u;  // bit q to byte q
+                    float *Pt = P + (ut + uf) + oP;
+                    uint8_t *St = S + (ut + uf) + oP;
+                    if (al) {
+                        if (P) *reinterpret_cast<f4 *>(Pt) = v;
+                        if (S) *reinterpret_cast<uint32_t *>(St) = sp;
+                    } else {
+                        if (P) *reinterpret_cast<PackedF4 *>(Pt) = PackedF4{{v[0], v[1], v[2], v[3]}};
+                        if (S) reinterpret_cast<PackedU4 *>(St)->w = sp;
+                    }
+                    if (fresh) {
+                        uint8_t *Tf = TF + uf + oF;
+                        float *Vf = VF + uf + oF;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if ((fresh >> q) & 1u) {
+                                Tf[q] = (uint8_t)t;
+                                Vf[q] = v[q];
+                            }
+                    }
+                } else {
+                    const int64_t fo = (int64_t)(f0 + tid / PG + half * 32 + m * FSTEP) * g.HoWo;
+                    for (int q = 0; q < nq; ++q) {
+                        // the quad ends in a later image
+                        int gq0 = gp0;
+                        asm volatile("" : "+v"(gq0));
+                        const int bq = (gq0 + q) / g.HoWo;
+                        const int64_t e = fo + gq0 + q - bq * g.HoWo, oq = ((int64_t)bq * g.T + t) * fplane + e;
+                        const float x = q == 0 ? v[0] : q == 1 ? v[1] : q == 2 ? v[2] : v[3];
+                        if (P) P[oq] = x;
+                        if (S) S[oq] = (uint8_t)((fire >> q) & 1u);
+                        if ((fresh >> q) & 1u) {
+                            TF[bq * fplane + e] = (uint8_t)t;
+                            VF[bq * fplane + e] = x;
+                        }
+                    }
+                }
+            }
+        };
+        auto zero_acc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int n = 0; n < NTL; ++n)
+#pragma unroll
+                    for (int t = 0; t < TB; ++t) acc[i][n][t] = f4{0.f, 0.f, 0.f, 0.f};
+        };
+        auto finish = [&](int tb0) __attribute__((always_inline)) {  // the block's accumulators out by the staging area
+            for (int s = 0; s < TG; ++s) {
+#pragma unroll
+                for (int t = 0; t < TB; ++t) {
+                    if (tb0 + s * TB + t >= g.T) break;  // uniform
+#pragma unroll
+                    for (int half = 0; half < NTL / 2; ++half) {
+                        if (TG == 1 || tg == s) {
+#pragma unroll
+                            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                                for (int n = 0; n < 2; ++n)
+                                    *reinterpret_cast<f4 *>(stage + (n * 16 + c) * SP + (wv * MT + i) * 16 + gq * 4) =
+                                        acc[i][2 * half + n][t] * inv_s;
+                        }
+                        lds_barrier();
+                        store(tb0 + s * TB + t, half);
+                        lds_barrier();
+                    }
+                }
+            }
+        };
+        uint32_t cur[KC][MT][2], nxt[KC][MT][2];
+        if (!ALDS) words(0, nxt);
+        fill(0, 0);
+        int buf = 0;
+        for (int tb0 = 0; tb0 < g.T; tb0 += TB * TG) {
+            zero_acc();
+            for (int ch = 0; ch < nch; ++ch) {
+                // this wave's transfers of the chunk (and its words) landed; with ALDS a block's first
+                // ones were waited for before the last block's stores, which need no wait themselves
+                if (ALDS) {
+                    if (ch > 0 || tb0 == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                } else {
+                    str_landed<KC, MT>(nxt);
+#pragma unroll
+                    for (int k = 0; k < KC; ++k)
+#pragma unroll
+                        for (int i = 0; i < MT; ++i) {
+                            cur[k][i][0] = nxt[k][i][0];
+                            cur[k][i][1] = nxt[k][i][1];
+                        }
+                }
+                lds_barrier();  // every wave's part of the chunk is in LDS, the other buffer is free
+                // (the last chunk of all is followed by a needless first one)
+                const int ch1 = ch + 1 < nch ? ch + 1 : 0;
+                if (!ALDS) words(ch1, nxt);
+                fill(ch1, buf ^ 1);
+                if (ALDS) words(ch, cur);
+                products(ch, buf, tb0, cur);
+                buf ^= 1;
+            }
+            if (ALDS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            finish(tb0);
+        }
+        // neurons that never fired
+        if (nq > 0) {
+#pragma unroll
+            for (int j = 0; j < M * (NTL / 2); ++j) {
+                const int f = f0 + j / M * 32 + tid / PG + j % M * FSTEP;
+                if (f >= g.Cout) continue;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (q < nq && !((fired >> (4 * j + q)) & 1u)) {
+                        const int bq = (gp0 + q) / g.HoWo;
+                        const int64_t o = bq * fplane + (int64_t)f * g.HoWo + gp0 + q - bq * g.HoWo;
+                        TF[o] = (uint8_t)g.T;
+                        VF[o] = 0.0f;
+                    }
+            }
+        }
+    };
+    if (kind == WK_BF16)
+        run(std::integral_constant<int, WK_BF16>{});
+    else
+        run(std::integral_constant<int, WK_F16>{});
+}
+
 // ------------------------------------------------------------------ 3b. infinite threshold (Eq.5)
 // Only the last step is computed: P[T-1] = sum_k W[f,k] [tp_k <= T-1], spike
 // where P[T-1] > 0.  Every earlier step holds zero potential and no spike;
@@ -1801,6 +2154,52 @@ void launch_fin(const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const
                        wbf16, wts, wmax, wmin, n_wmax, P, S, TF, VF, po, arith);
 }
 
+// The form of a call: fp32, fused pooling, or plain (whose weights are in LDS:
+// those that do not fit are streamed).
+template <int G, bool BLDS, bool ALDS>
+void launch_fin_form(bool pooled, const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const float *inv_scale,
+                     const int *wbf16, const float *wts, const unsigned *wmax, const unsigned *wmin, int n_wmax,
+                     const ConvGeom &g, int n_pairs, int n_chunks, int cpi, int chunk_tiles, int band_pos, int np_max,
+                     int a_words, size_t lds, float *P, uint8_t *S, uint8_t *TF, float *VF, const PoolOut &po,
+                     int arith, hipStream_t st) {
+    auto launch = [&](auto mode) {
+        launch_fin<G, BLDS, ALDS, decltype(mode)::value>(tpad, frag, koff2, inv_scale, wbf16, wts, wmax, wmin, n_wmax,
+                                                         g, n_pairs, n_chunks, cpi, chunk_tiles, band_pos, np_max,
+                                                         a_words, lds, P, S, TF, VF, po, arith, st);
+    };
+    if (arith == 1)
+        launch(std::integral_constant<int, FIN_F32>{});
+    else if (pooled)
+        launch(std::integral_constant<int, FIN_POOL>{});
+    else if constexpr (BLDS)
+        launch(std::integral_constant<int, FIN_SPLIT>{});
+}
+
+// Rows of the padded map that the windows of `cpos` consecutive positions touch, at
+// most: R output rows further and d images on, the last window starts
+// d Hp + (R - d Ho) S rows after the first.
+int64_t rows_of_positions(const ConvGeom &g, int cpos) {
+    const int64_t R = ((int64_t)cpos + g.Wo - 2) / g.Wo, d = ((int64_t)cpos + g.HoWo - 2) / g.HoWo;
+    return R * g.S + g.K + d * std::max(0, g.Hp - g.Ho * g.S);
+}
+
+template <int MT, int NTL, int TG>
+void launch_str(const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const float *inv_scale, const int *wbf16,
+                const ConvGeom &g, float *P, uint8_t *S, uint8_t *TF, float *VF, hipStream_t st) {
+    const int n_fg = (int)spk::ceil_div(g.Cout, 16 * NTL);
+    const int n_chunks = (int)spk::ceil_div((int64_t)g.B * g.HoWo, 64 * MT);
+    const dim3 grid((unsigned)((n_chunks + 7) / 8 * n_fg * 8));
+    // the rows in LDS when two workgroups per CU still fit, else the words from L2
+    const size_t rows = (size_t)rows_of_positions(g, 64 * MT) * g.Wp * g.CP;
+    const size_t with = str_lds(MT, NTL, g.ksteps, spk::align_up(rows, 16));
+    if (with <= (TG == 4 ? 160 : 80) * 1024)
+        hipLaunchKernelGGL((k_conv_fire_str<MT, NTL, TG, true>), grid, dim3(256 * TG), with, st, tpad, frag, koff2, g,
+                           n_fg, n_chunks, inv_scale, wbf16, P, S, TF, VF);
+    else
+        hipLaunchKernelGGL((k_conv_fire_str<MT, NTL, TG, false>), grid, dim3(256 * TG), str_lds(MT, NTL, g.ksteps, 0),
+                           st, tpad, frag, koff2, g, n_fg, n_chunks, inv_scale, wbf16, P, S, TF, VF);
+}
+
 // Position-major Eq.5 tasks pay when most of the receptive fields' K-steps are
 // padding and there are enough (feature group, position, image block) tasks.
 int inf_pm_nib(const ConvGeom &g, int ksplit) {
@@ -2010,6 +2409,7 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
                            (inf_pm_nib(g, pl.ksplit) ? 2 * (size_t)g.ksteps * 4 * sizeof(int2) : 0);
     SPK_REQUIRE(!inf_mode || inf_lds <= lds_limit, SPK_E_RANGE,
                 "spk_conv_fire: needs %zu bytes of LDS per workgroup, the device has %zu", inf_lds, lds_limit);
+    const bool streamed = !inf_mode && !pooled && arith == 0 && !blds;
     SPK_REQUIRE(inf_mode || fin_lds <= lds_limit, SPK_E_RANGE,
                 "spk_conv_fire: needs %zu bytes of LDS per workgroup, the device has %zu", fin_lds, lds_limit);
 
@@ -2028,7 +2428,7 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
     else
         hipLaunchKernelGGL(k_pad_first_spike<false>, pad_grid, dim3(256), pad_lds, st, wave, g, rows_per_chunk, nchunk, ny,
                            tpad, weight, nw, wper, wmax, wmin);
-    if (inf_mode || !blds) {  // fragments in the workspace (the finite-threshold kernel with LDS room builds its own)
+    if (inf_mode || !blds || streamed) {  // fragments in the workspace (the finite-threshold kernel with LDS room builds its own)
         if (g.CP % 32 == 0 && arith != 1) {
             hipLaunchKernelGGL(k_split_weights_cells, dim3((unsigned)(g.ntiles * (g.CP / 8))), dim3(256), 0, st, weight,
                                g, wmax, wmin, n_wmax, frag, koff2, inv_scale, wbf16);
@@ -2045,22 +2445,32 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
         else
             launch_inf<false>(tpad, frag, koff2, inv_scale, wbf16, g, pl.ksplit, pl.kpp, part, potentials, spikes,
                               t_first, v_first, st);
+    } else if (streamed) {
+        // Groups of 64 features and 128 positions where they fill the chip twice and waste no
+        // more features than groups of 32 would: the fewest LDS reads a product (64 256x256 maps,
+        // 256 features of 5x5: 5.0 ms, 64 positions x 64 features with two groups of waves 6.1 ms).
+        // Else 64 positions x 32 features, with two groups of waves a workgroup (31 65x43 maps, 70
+        // features of 7x7, stride 2: 202 us; with one 237, 128 positions with one 307 or two 281,
+        // 256 positions with one 386), or four where the workgroups are fewer than the CUs (1 to 64
+        // images of the natural layer: 321 against 326 us a step), as far as there are steps.
+        const int64_t np64 = spk::ceil_div(npos, 64);
+        const int fg4 = (int)spk::ceil_div(Cout, 64), fg2 = (int)spk::ceil_div(Cout, 32);
+#define SPK_STR(MT, NTL, TG) \
+    launch_str<MT, NTL, TG>(tpad, frag, koff2, inv_scale, wbf16, g, potentials, spikes, t_first, v_first, st)
+        if (2 * fg4 == fg2 && np64 / 2 * fg4 >= 512)
+            SPK_STR(2, 4, 1);
+        else if (T <= STR_TB)
+            SPK_STR(1, 2, 1);
+        else if (np64 * fg2 > 256 || T <= 2 * STR_TB)
+            SPK_STR(1, 2, 2);
+        else
+            SPK_STR(1, 2, 4);
+#undef SPK_STR
     } else {
-#define SPK_FIN(G, BL, AL)                                                                                        \
-    do {                                                                                                          \
-        if (arith == 1)                                                                                           \
-            launch_fin<G, BL, AL, FIN_F32>(tpad, frag, koff2, inv_scale, wbf16, weight, wmax, wmin, n_wmax, g,      \
-                                           n_pairs, n_chunks, cpi, chunk_tiles, band_pos, np_max, a_words, fin_lds, \
-                                           potentials, spikes, t_first, v_first, pool, arith, st);                  \
-        else if (pooled)                                                                                          \
-            launch_fin<G, BL, AL, FIN_POOL>(tpad, frag, koff2, inv_scale, wbf16, weight, wmax, wmin, n_wmax, g,     \
-                                            n_pairs, n_chunks, cpi, chunk_tiles, band_pos, np_max, a_words,         \
-                                            fin_lds, potentials, spikes, t_first, v_first, pool, arith, st);        \
-        else                                                                                                      \
-            launch_fin<G, BL, AL, FIN_SPLIT>(tpad, frag, koff2, inv_scale, wbf16, weight, wmax, wmin, n_wmax, g,    \
-                                             n_pairs, n_chunks, cpi, chunk_tiles, band_pos, np_max, a_words,        \
-                                             fin_lds, potentials, spikes, t_first, v_first, pool, arith, st);       \
-    } while (0)
+#define SPK_FIN(G, BL, AL)                                                                                          \
+    launch_fin_form<G, BL, AL>(pooled, tpad, frag, koff2, inv_scale, wbf16, weight, wmax, wmin, n_wmax, g, n_pairs,   \
+                               n_chunks, cpi, chunk_tiles, band_pos, np_max, a_words, fin_lds, potentials, spikes,    \
+                               t_first, v_first, pool, arith, st)
         const int sel = (vec ? 4 : 0) + (blds ? 2 : 0) + (alds ? 1 : 0);
         switch (sel) {
             case 0: SPK_FIN(1, false, false); break;

@@ -96,6 +96,56 @@ CONV_CASES = [
 ]
 
 
+# Layers whose weight fragments are streamed (a feature pair's past LDS): every feature group size and
+# number of wave groups, chunks that end inside an image and maps of 1 to 3 positions (a quad of
+# positions then spans images), K-steps that are no whole chunk, steps that are no whole block
+STREAM_CASES = [
+    # name, B, T, Cin, H, W, Cout, K, pad, stride, thr, p_silent
+    ("groups-of-64", 64, 4, 64, 16, 16, 256, 3, 1, 1, 30.0, 0.6),
+    ("groups-of-64-words-from-L2", 8, 2, 160, 46, 46, 256, 3, 1, 1, 60.0, 0.6),
+    ("one-wave-group", 24, 3, 13, 65, 43, 70, 7, 3, 2, 20.0, 0.6),
+    ("two-wave-groups", 90, 7, 4, 26, 41, 20, 17, 0, 1, 36.0, 0.5),
+    ("two-wave-groups-words-from-L2", 2, 5, 160, 26, 25, 40, 5, 2, 1, 60.0, 0.6),
+    ("four-wave-groups", 3, 17, 4, 26, 41, 20, 17, 0, 1, 36.0, 0.5),
+    ("one-position", 37, 5, 140, 3, 3, 33, 3, 0, 1, 60.0, 0.5),
+    ("three-positions", 70, 13, 150, 3, 5, 17, 3, 0, 1, 60.0, 0.5),
+    ("two-by-one", 9, 1, 160, 4, 3, 65, 3, 0, 1, 10.0, 0.3),
+    ("T-255", 1, 255, 200, 5, 6, 20, 3, 1, 1, 60.0, 0.2),
+]
+
+
+@pytest.mark.parametrize("case", STREAM_CASES, ids=[c[0] for c in STREAM_CASES])
+@pytest.mark.parametrize("kind", ["normal", "dyadic", "bf16"])
+def test_conv_fire_streamed_weights(case, kind, near_log):
+    name, B, T, Cin, H, W, Cout, K, pad, stride, thr, ps = case
+    g = synth.rng(190 + len(name), 1)
+    tf = synth.times_uniform_or_silent(g, (B, Cin, H, W), T, ps)
+    shape = (Cout, Cin, K, K)
+    if kind == "normal":
+        Wt = synth.normal_weights(g, shape, 0.8, 0.05)
+    else:  # exactly summable
+        Wt = synth.dyadic_weights(g, shape, Cin * K * K) if kind == "dyadic" else weights.wide_range_dyadic(
+            g, shape, Cin * K * K)
+    # (the oracle takes the first, a middle and the last image of the larger cases)
+    Ho, Wo = (H + 2 * pad - K) // stride + 1, (W + 2 * pad - K) // stride + 1
+    pick = sorted({0, B // 2, B - 1}) if B * Ho * Wo * Cout * Cin * K * K > 5e8 else list(range(B))
+    ref = orc.conv_fire(wave_of(tf[pick], T), Wt, pad, thr, stride)
+    got = spk.spk_conv_fire_first_spike_strided(dev(tf), T, dev(Wt), stride, pad, thr)
+    lone = spk.spk_conv_fire_first_spike_strided(dev(tf), T, dev(Wt), stride, pad, thr, potentials=False, spikes=False)
+    odd = [dev_shifted(np.zeros(tuple(x.shape), r.dtype)) for x, r in zip(got, ref)]
+    spk.spk_conv_fire_first_spike_strided(dev(tf), T, dev(Wt), stride, pad, thr, *odd)
+    sync()
+    near_log(f"conv streamed {name}/{kind}",
+             compare_conv_fire(tuple(host(x)[pick] for x in got), ref, thr, exact_potentials=kind != "normal"),
+             ref[2].size)
+    if kind != "normal":
+        for x, r, what in zip(got, ref, ("P", "S", "t_first", "v_first")):
+            assert_equal(host(x)[pick], r, what)
+    assert torch.equal(lone[2], got[2]) and torch.equal(lone[3], got[3])
+    for x, o in zip(got, odd):
+        assert torch.equal(x, o), "unaligned outputs"
+
+
 def fin_task_form(B, Cout, Ho, Wo):
     """How the finite-threshold conv call cuts its work (a restatement of the
     host plan): ("image", split) when each task is one whole image, split being
