@@ -198,14 +198,34 @@ __global__ __launch_bounds__(256) void k_pad_first_spike(const uint8_t *__restri
         for (int i = tid * 4; i < shift + nbytes; i += 1024) *reinterpret_cast<uint32_t *>(buf + i) = tfill;
         __syncthreads();
         const uint8_t *src = wave + b * (TIMES ? 1 : g.T) * (int64_t)g.Cin * hw;
-        // A whole image's first-spike map is one contiguous block: it is read
-        // with word loads, all issued before any is used, into LDS first.
-        const bool staged = TIMES && pad_raw_fits(g, nchunk) && ((uintptr_t)src & 3) == 0;
+        // A whole image's map (or step of its wave) is one contiguous block: it is read
+        // with word loads, all issued before any is used, into LDS first, a wave as its
+        // first-spike times of 4 cells at once, T - the number of ones in each byte
+        // over the steps (byte loads cell by cell took 45 us for 256 images of 30
+        // maps of 14x14, T = 15, words 16).
+        const bool staged = pad_raw_fits(g, nchunk) && ((uintptr_t)src & 3) == 0;
         if (staged) {
             const int nwd = g.Cin * hw / 4;
             const uint32_t *s4 = reinterpret_cast<const uint32_t *>(src);
             uint32_t *r4 = reinterpret_cast<uint32_t *>(raw);
-            for (int i0 = tid; i0 < nwd; i0 += 8 * 256) {
+            for (int i0 = tid; i0 < (TIMES ? 0 : nwd); i0 += 256) {
+                uint32_t cnt = 0;
+                for (int t0 = 0; t0 < g.T; t0 += 16) {
+                    uint32_t v[16];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) v[u] = s4[(int64_t)min(t0 + u, g.T - 1) * nwd + i0];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) {
+                        uint32_t x = t0 + u < g.T ? v[u] : 0u;  // any non-zero byte counts one
+                        x |= (x >> 4) & 0x0F0F0F0Fu;
+                        x |= (x >> 2) & 0x03030303u;
+                        x |= (x >> 1) & 0x01010101u;
+                        cnt += x & 0x01010101u;
+                    }
+                }
+                r4[i0] = (uint32_t)g.T * 0x01010101u - cnt;
+            }
+            for (int i0 = tid; i0 < (TIMES ? nwd : 0); i0 += 8 * 256) {
                 uint32_t v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = s4[min(i0 + 256 * u, nwd - 1)];  // (clamped: unconditional)
