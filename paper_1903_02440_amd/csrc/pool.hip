@@ -9,6 +9,7 @@
 // step t it ORs the window's bytes of plane t and stores one byte, so a wave
 // reads and writes consecutive x positions of one plane; the first-spike map
 // is T minus the number of steps at which the pooled neuron is on.
+#include <algorithm>
 #include <cstdint>
 
 #include "common.hpp"
@@ -42,6 +43,120 @@ __global__ __launch_bounds__(256) void k_pool(const uint8_t *__restrict__ in, in
         on += m;
     }
     if (out_tf) out_tf[b * per_img + i] = (uint8_t)(T - on);
+}
+
+// The same with the input staged in LDS: a workgroup takes CB whole maps of one
+// image (contiguous in every step) and goes through the steps, copying the next
+// step's bytes with 16-byte loads at any alignment while the current ones are
+// pooled, 4 consecutive outputs per thread (at most WL_QUADS times) in one 4-byte
+// store.  Bound by reading the wave: 256 images of 250 maps of 14x14, T = 15, 3x3
+// windows, took 150 us with one output per thread from single byte loads, now 74 us
+// (233 MB, 3.2 TB/s).
+constexpr int WL_BYTES = 16384;  // input bytes of a step at most
+constexpr int WL_QUADS = 2;      // quads of outputs per thread
+constexpr int WL_LOADS = WL_BYTES / 16 / 256;
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t w[4];
+};
+struct __attribute__((packed, aligned(1))) Bytes4 {
+    uint32_t w;
+};
+template <int PW, bool IN>  // IN: no padding, every window lies in its map
+__global__ __launch_bounds__(256) void k_pool_lds(const uint8_t *__restrict__ in, int T, int C, int H, int W, int P,
+                                                  int R, int D, int Ho, int Wo, int CB, uint8_t *__restrict__ out,
+                                                  uint8_t *__restrict__ out_tf) {
+    __shared__ uint4 lds[WL_BYTES / 16];
+    uint8_t *lt = reinterpret_cast<uint8_t *>(lds);
+    const int tid = threadIdx.x, nblk = (C + CB - 1) / CB;
+    const int64_t b = blockIdx.x / nblk;
+    const int c0 = (int)(blockIdx.x % nblk) * CB, cb = min(CB, C - c0), HW = H * W, hw = Ho * Wo;
+    const int nbytes = cb * HW, nout = cb * hw;
+    const int64_t in_plane = (int64_t)C * HW, out_plane = (int64_t)C * hw;
+    const uint8_t *src = in + b * T * in_plane + (int64_t)c0 * HW;
+    uint8_t *dst = out + b * T * out_plane + (int64_t)c0 * hw;
+    const int n16 = nbytes / 16, rest = nbytes - 16 * n16;  // whole 16 bytes, then single ones
+    uint4 v[WL_LOADS];
+    uint8_t vb = 0;
+    auto load = [&](int t) {
+        const uint8_t *s = src + t * in_plane;
+#pragma unroll
+        for (int k = 0; k < WL_LOADS; ++k) {
+            const int i = tid + k * 256;
+            if (i < n16) {
+                const Bytes16 x = *reinterpret_cast<const Bytes16 *>(s + 16 * i);
+                v[k] = uint4{x.w[0], x.w[1], x.w[2], x.w[3]};
+            }
+        }
+        if (tid < rest) vb = s[16 * n16 + tid];
+    };
+    uint32_t on[WL_QUADS];  // steps at which each output of a quad is on, a byte each
+#pragma unroll
+    for (int m = 0; m < WL_QUADS; ++m) on[m] = 0;
+    int at[WL_QUADS][4];  // IN: each output's window corner in LDS (outputs past the block: the first's)
+#pragma unroll
+    for (int m = 0; m < WL_QUADS; ++m)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int j = (tid + m * 256) * 4 + q, jj = j < nout ? j : 0;
+            const int c = jj / hw, yo = (jj - c * hw) / Wo, xo = jj - c * hw - yo * Wo;
+            at[m][q] = IN ? c * HW + yo * R * W + xo * R : c << 20 | yo << 10 | xo;
+        }
+    load(0);
+    for (int t = 0; t < T; ++t) {
+#pragma unroll
+        for (int k = 0; k < WL_LOADS; ++k)
+            if (tid + k * 256 < n16) lds[tid + k * 256] = v[k];
+        if (tid < rest) lt[16 * n16 + tid] = vb;
+        __syncthreads();
+        if (t + 1 < T) load(t + 1);
+#pragma unroll
+        for (int m = 0; m < WL_QUADS; ++m) {
+            const int j0 = (tid + m * 256) * 4;
+            if (j0 >= nout) continue;
+            uint32_t o4 = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                uint32_t any = 0;
+                if (IN) {
+                    const uint8_t *w = lt + at[m][q];
+                    if (PW > 0) {
+#pragma unroll
+                        for (int dy = 0; dy < PW; ++dy)
+#pragma unroll
+                            for (int dx = 0; dx < PW; ++dx) any |= w[dy * W + dx];
+                    } else {
+#pragma unroll 1
+                        for (int dy = 0; dy < P; ++dy)
+#pragma unroll 1
+                            for (int dx = 0; dx < P; ++dx) any |= w[dy * W + dx];
+                    }
+                } else {
+                    const int y0 = ((at[m][q] >> 10) & 1023) * R - D, x0 = (at[m][q] & 1023) * R - D;
+                    const uint8_t *pl = lt + (at[m][q] >> 20) * HW;
+                    for (int y = max(y0, 0); y < min(y0 + P, H); ++y)
+                        for (int x = max(x0, 0); x < min(x0 + P, W); ++x) any |= pl[y * W + x];
+                }
+                o4 |= (any != 0 ? 1u : 0u) << (8 * q);
+            }
+            on[m] += o4;
+            uint8_t *d = dst + t * out_plane + j0;
+            if (j0 + 4 <= nout) {
+                reinterpret_cast<Bytes4 *>(d)->w = o4;
+            } else {
+                for (int q = 0; j0 + q < nout; ++q) d[q] = (uint8_t)(o4 >> (8 * q));
+            }
+        }
+        __syncthreads();
+    }
+    if (out_tf)
+#pragma unroll
+        for (int m = 0; m < WL_QUADS; ++m) {
+            const int j0 = (tid + m * 256) * 4;
+            if (j0 >= nout) continue;
+            const uint32_t t4 = (uint32_t)T * 0x01010101u - on[m];
+            uint8_t *d = out_tf + b * out_plane + (int64_t)c0 * hw + j0;
+            for (int q = 0; q < 4 && j0 + q < nout; ++q) d[q] = (uint8_t)(t4 >> (8 * q));
+        }
 }
 
 // Pooling of first-spike maps: the minimum over the window, then its T wave
@@ -249,6 +364,22 @@ extern "C" int spk_pool(const uint8_t *wave, int B, int T, int C, int H, int W, 
     SPK_REQUIRE(wave && out_wave, SPK_E_ARG, "spk_pool: wave and out_wave are required");
     const int64_t per_img = (int64_t)C * Ho * Wo;
     SPK_REQUIRE(per_img <= 65535LL * 256 && (int64_t)C * H * W < (1LL << 31), SPK_E_RANGE, "spk_pool: image too large");
+    const int64_t HW = (int64_t)H * W, hw = (int64_t)Ho * Wo;
+    if (HW <= WL_BYTES && hw <= WL_QUADS * 1024 && Ho < 1024 && Wo < 1024) {  // whole maps through LDS
+        const int CB = (int)std::min<int64_t>({(int64_t)C, WL_BYTES / HW, WL_QUADS * 1024 / hw, (int64_t)2047});
+        const int64_t blocks = (int64_t)B * spk::ceil_div(C, CB);
+        if (blocks < (1LL << 31)) {
+#define SPK_POOL_WAVE(PW, IN)                                                                                          \
+    hipLaunchKernelGGL((k_pool_lds<PW, IN>), dim3((unsigned)blocks), dim3(256), 0, spk::as_stream(stream), wave, T, C, \
+                       H, W, kernel, stride, pad, Ho, Wo, CB, out_wave, out_t_first)
+            if (pad > 0) SPK_POOL_WAVE(0, false);
+            else if (kernel == 2) SPK_POOL_WAVE(2, true);
+            else if (kernel == 3) SPK_POOL_WAVE(3, true);
+            else SPK_POOL_WAVE(0, true);
+#undef SPK_POOL_WAVE
+            return spk::check_launch("spk_pool");
+        }
+    }
     hipLaunchKernelGGL(k_pool, dim3((unsigned)B, (unsigned)spk::ceil_div(per_img, 256)), dim3(256), 0,
                        spk::as_stream(stream), wave, T, C, H, W, kernel, stride, pad, Ho, Wo, out_wave, out_t_first);
     return spk::check_launch("spk_pool");

@@ -336,7 +336,11 @@ POOL_CASES = [(3, 15, 30, 28, 28, 2, 2, 0), (2, 15, 250, 14, 14, 3, 3, 0), (2, 3
               (2, 7, 3, 9, 10, 3, 2, 1), (1, 5, 2, 5, 5, 5, 1, 2), (2, 3, 1, 1, 1, 1, 1, 0),
               (2, 9, 8, 12, 12, 4, 2, 1), (2, 5, 12, 10, 10, 2, 2, 0),
               # batches of a few hundred images
-              (256, 15, 30, 8, 8, 2, 2, 0), (260, 15, 25, 9, 9, 3, 3, 0)]
+              (256, 15, 30, 8, 8, 2, 2, 0), (260, 15, 25, 9, 9, 3, 3, 0),
+              # waves through LDS: blocks of maps that end in the last bytes and outputs of no whole
+              # quad, one map a block, more outputs than inputs; a map past LDS; T > 127
+              (2, 15, 37, 13, 11, 3, 3, 0), (1, 4, 3, 127, 129, 5, 4, 2), (2, 200, 5, 6, 7, 2, 1, 1),
+              (1, 3, 2, 130, 130, 3, 3, 0), (3, 15, 130, 3, 5, 2, 2, 0), (1, 3, 2, 60, 60, 2, 1, 0)]
 
 
 @pytest.mark.parametrize("case", POOL_CASES)
@@ -350,6 +354,9 @@ def test_pool_parity(case):
     ref = orc.pool(wave, P, R, D)
     assert_equal(host(out), ref, "pooled wave")
     assert_equal(host(otf), orc.first_spike(ref), "pooled t_first")
+    so, _ = spk.spk_pool(dev_shifted(wave), P, R, D, out_wave=dev_shifted(np.zeros_like(ref)))
+    sync()
+    assert_equal(host(so), ref, "pooled wave, unaligned")
 
 
 @pytest.mark.parametrize("case", POOL_CASES)
