@@ -162,22 +162,35 @@ __global__ __launch_bounds__(TOPK_THREADS_SMALL_B) void k_kwta_topk(const uint8_
     int32_t *win = winners + (int64_t)b * g.k * 4;
     for (int i = tid; i < 4 * g.k; i += NT) win[i] = -1;
 
-    if (g.ns > 1) {  // the lists of the workgroup splits, merged (each is sorted)
-        for (int p = tid; p < HW; p += NT) {
-            uint64_t top[KM];
+    // The lists of the workgroup splits, merged (each is sorted), MB of them read whole
+    // before the first is merged: an entry at a time, each waited for, one image of 250
+    // maps of 14x14, k = 8, took 24.7 us, now 22.2.  (Several threads per position, their
+    // lists merged again by the owner: 29 us.)
+    for (int p = tid; p < (g.ns > 1 ? HW : 0); p += NT) {
+        constexpr int MB = KM <= 8 ? 4 : KM <= 12 ? 2 : 1;
+        uint64_t top[KM];
 #pragma unroll
-            for (int i = 0; i < KM; ++i) top[i] = 0;
-            for (int sp = 0; sp < g.ns; ++sp) {
-                const uint64_t *src = g.lg + (((int64_t)b * g.ns + sp) * HW + p) * KM;
-                for (int e = 0; e < KM; ++e) {
-                    const uint64_t key = src[e];
-                    if (!(key > top[KM - 1])) break;
-                    topk_insert(top, key);
-                }
+        for (int i = 0; i < KM; ++i) top[i] = 0;
+        for (int sp0 = 0; sp0 < g.ns; sp0 += MB) {
+            uint64_t kk[MB][KM];
+#pragma unroll
+            for (int q = 0; q < MB; ++q) {
+                const uint64_t *src = g.lg + (((int64_t)b * g.ns + min(sp0 + q, g.ns - 1)) * HW + p) * KM;
+#pragma unroll
+                for (int e = 0; e < KM; ++e) kk[q][e] = src[e];
             }
 #pragma unroll
-            for (int i = 0; i < KM; ++i) lists[(size_t)p * KM + i] = top[i];
+            for (int q = 0; q < MB; ++q) {
+                if (sp0 + q >= g.ns) break;
+#pragma unroll
+                for (int e = 0; e < KM; ++e) {
+                    if (!(kk[q][e] > top[KM - 1])) break;
+                    topk_insert(top, kk[q][e]);
+                }
+            }
         }
+#pragma unroll
+        for (int i = 0; i < KM; ++i) lists[(size_t)p * KM + i] = top[i];
     }
     // pass over the image: the KM best keys of every (position, feature split)
     for (int pp = tid; pp < (g.ns > 1 ? 0 : HW * S); pp += NT) {
