@@ -40,8 +40,10 @@
 //      per-lane word offsets of every 8-tap group: built by the
 //      finite-threshold kernel itself when its fragments fit in LDS, else by
 //      k_split_weights into the workspace.
-//   3. finite threshold: k_conv_fire_fin (below); threshold = +inf (Eq.5):
-//      k_conv_fire_inf, which computes only the last step.
+//   3. finite threshold: k_conv_fire_fin when the fragments fit in LDS (and in
+//      its pooled and fp32 forms), else k_conv_fire_str, which streams them
+//      (both below); threshold = +inf (Eq.5): k_conv_fire_inf, which computes
+//      only the last step.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -585,7 +587,7 @@ __device__ __forceinline__ f4 mfma(u4 a, uint4 b, f4 c) {
 //   * each MFMA wave computes the GEMM of its tiles (local tiles w and w+8)
 //     for the 32 features and TB steps -- spike words from the task's rows,
 //     staged in LDS one task ahead (or straight from tpad), weight fragments
-//     from LDS (or L2 when they do not fit) -- and writes the scaled
+//     from LDS (L2 in the pooled and fp32 forms when they do not fit) -- and writes the scaled
 //     potentials into the LDS staging area [TB][32 features][row stride];
 //   * the store waves then fire the staged potentials (threshold, first spike,
 //     potential at the first spike, kept in their registers for the whole

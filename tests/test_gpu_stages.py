@@ -126,9 +126,9 @@ def test_conv_fire_streamed_weights(case, kind, near_log):
     else:  # exactly summable
         Wt = synth.dyadic_weights(g, shape, Cin * K * K) if kind == "dyadic" else weights.wide_range_dyadic(
             g, shape, Cin * K * K)
-    # (the oracle takes the first, a middle and the last image of the larger cases)
+    # (the oracle takes the first and the last image of the larger cases)
     Ho, Wo = (H + 2 * pad - K) // stride + 1, (W + 2 * pad - K) // stride + 1
-    pick = sorted({0, B // 2, B - 1}) if B * Ho * Wo * Cout * Cin * K * K > 5e8 else list(range(B))
+    pick = sorted({0, B - 1}) if B * Ho * Wo * Cout * Cin * K * K > 5e8 else list(range(B))
     ref = orc.conv_fire(wave_of(tf[pick], T), Wt, pad, thr, stride)
     got = spk.spk_conv_fire_first_spike_strided(dev(tf), T, dev(Wt), stride, pad, thr)
     lone = spk.spk_conv_fire_first_spike_strided(dev(tf), T, dev(Wt), stride, pad, thr, potentials=False, spikes=False)
