@@ -32,8 +32,8 @@ struct __attribute__((packed, aligned(4))) Float4u {
 // zeros over the potentials of every feature that is no winner.  Nearly all of
 // that is constant, so nothing is read again.  All inputs of the locations are
 // read before any output is written and the parts of a run are only more than
-// one when the outputs are not the inputs, so the first-spike outputs may alias
-// the inputs.
+// one when no output lies over an input, so the outputs may alias the inputs
+// (the first-spike ones, or at one step the wave and the potentials).
 // Bound by the writes (5 (1 + T) bytes a neuron with wave and potentials).  With
 // one thread per 4 locations doing all of it (the form before), 200 images of 250
 // maps of 14x14 kept 39 workgroups busy and read the potentials: 1444 us; now
@@ -263,8 +263,11 @@ extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_f
         const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
         return x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
     };
-    const bool alias = overlap(out_t_first, N, t_first, N) || overlap(out_t_first, N, v_first, 4 * N) ||
-                       overlap(out_v_first, 4 * N, t_first, N) || overlap(out_v_first, 4 * N, v_first, 4 * N);
+    auto on_inputs = [&](const void *out, int64_t bytes) {
+        return out && (overlap(out, bytes, t_first, N) || overlap(out, bytes, v_first, 4 * N));
+    };
+    const bool alias = on_inputs(out_t_first, N) || on_inputs(out_v_first, 4 * N) || on_inputs(out_wave, T * N) ||
+                       on_inputs(potentials, 4 * T * N);
     const int64_t per_run = spk::ceil_div((int64_t)C * spk::ceil_div(std::min<int64_t>(HW, PW_LOC), 4), PW_THREADS);
     const int64_t parts = alias ? 1 : std::max<int64_t>(1, std::min<int64_t>({1024 / (B * nrun), 8, per_run}));
     SPK_REQUIRE(B * nrun * parts < (1LL << 31), SPK_E_RANGE, "spk_pointwise_inhibition: too large");

@@ -434,6 +434,34 @@ def test_pointwise_inhibition_runs(case, put):
     assert_equal(host(gp), rp, "masked potentials")
 
 
+@pytest.mark.parametrize("shape,T", [((3, 250, 14, 14), 1), ((1, 250, 14, 14), 15), ((2, 64, 40, 41), 1)])
+def test_pointwise_inhibition_outputs_over_inputs(shape, T):
+    # one step's potentials are the potentials at the first spike, and one step's wave has the size of
+    # the first-spike map; of one image, any step of the potentials may be the input.  All of a
+    # location's inputs are read before anything is written there, whichever output lies over them.
+    B, C, H, W = shape
+    g = synth.rng(740 + C + T, 0)
+    tf = synth.times_uniform_or_silent(g, shape, T, 0.5)
+    pot = g.normal(0, 3, (B, T, C, H, W)).astype(np.float32)
+    vf = np.ascontiguousarray(pot[:, T - 1])
+    rt, rv, rp = orc.pointwise_inhibition(tf, vf, T, pot)
+    gp = dev(pot)
+    over = gp[:, T - 1]
+    assert over.is_contiguous()
+    ot, ov, _ = spk.spk_pointwise_inhibition(dev(tf), over, T, potentials=gp)
+    sync()
+    assert_equal(host(ot), rt, "t_first, potentials over v_first")
+    assert_equal(host(ov), rv, "v_first, potentials over v_first")
+    assert_equal(host(gp), rp, "masked potentials over v_first")
+    if T == 1:
+        it = dev(tf)
+        ot, ov, ow = spk.spk_pointwise_inhibition(it, dev(vf), T, out_wave=it.view(B, T, C, H, W))
+        sync()
+        assert_equal(host(ot), rt, "t_first, wave over t_first")
+        assert_equal(host(ov), rv, "v_first, wave over t_first")
+        assert_equal(host(ow), orc.expand_wave(rt, T), "wave over t_first")
+
+
 # 2x2 windows of stride 2 on widths that are multiples of 4 take 16-byte loads of
 # two rows (the 28x28 map; an odd height, whose last row no window covers); the
 # rest one output per thread
