@@ -123,10 +123,10 @@ __global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, con
             const PwBest o = found[sp * 4 * nq + p];
             pw_join(a, o.t, o.c, o.first, o.v);
         }
-        const bool nan_first = a.first >= 0 && (a.first & 1);
+        const bool nan_first = p < n && a.first >= 0 && (a.first & 1);
         bc[p] = p < n ? (nan_first ? a.first >> 1 : a.c) : -1;
         bt[p] = (uint8_t)a.t;
-        bv[p] = nan_first ? __int_as_float(0x7FC00000) : a.v;
+        bv[p] = nan_first ? vf[base + (int64_t)(a.first >> 1) * HW + p] : a.v;  // (its own bits)
     }
     __syncthreads();
     const int64_t items = (int64_t)C * nq, i1 = items * (part + 1) / parts;

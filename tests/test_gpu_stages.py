@@ -434,6 +434,23 @@ def test_pointwise_inhibition_runs(case, put):
     assert_equal(host(gp), rp, "masked potentials")
 
 
+@pytest.mark.parametrize("shape", [(2, 5, 27, 38), (1, 9, 40, 41), (3, 7, 1, 1)])
+def test_pointwise_inhibition_copies_the_winners_bits(shape):
+    # a winner's potential is copied: one that is no number keeps its sign and payload
+    T = 3
+    g = synth.rng(730 + shape[1], 0)
+    tf = g.integers(0, T + 1, shape).astype(np.uint8)
+    vf = (g.integers(-3, 4, shape) * 0.5).astype(np.float32)
+    nan = g.random(shape) < 0.4
+    vf[nan] = (g.integers(0x7FC00000, 0x7FD00000, shape) | g.integers(0, 2, shape) << 31).astype(np.uint32).view(
+        np.float32)[nan]
+    rt, rv = orc.pointwise_inhibition(tf, vf, T)
+    ot, ov, _ = spk.spk_pointwise_inhibition(dev(tf), dev(vf), T)
+    sync()
+    assert_equal(host(ot), rt, "t_first")
+    assert_equal(host(ov).view(np.uint32), rv.view(np.uint32), "v_first (bits)")
+
+
 @pytest.mark.parametrize("shape,T", [((3, 250, 14, 14), 1), ((1, 250, 14, 14), 15), ((2, 64, 40, 41), 1)])
 def test_pointwise_inhibition_outputs_over_inputs(shape, T):
     # one step's potentials are the potentials at the first spike, and one step's wave has the size of
