@@ -23,7 +23,7 @@ struct __attribute__((packed, aligned(4))) Float4u {
     float v[4];
 };
 
-// Grid: (part, run of up to PW_LOC locations, image).  The workgroup first finds
+// Grid: (part, run of up to PW_LOC locations, image), from run u0 of all images' on.  The workgroup first finds
 // the winner of each of its locations over the C features (the kWTA order:
 // earlier spike, then larger potential, then lower feature index), 4 locations
 // and every n-th feature per thread, the threads' findings joined in LDS.  Then
@@ -60,19 +60,19 @@ __device__ __forceinline__ void pw_join(PwBest &a, int t, int c, int first, floa
     }
 }
 
-__global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, const float *vf, int T, int C, int HW,
-                                                          int nrun, int parts, uint8_t *out_t, float *out_v,
-                                                          uint8_t *wave, float *pot) {
+__global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, const float *vf, int T, int C, int64_t HW,
+                                                          int64_t u0, int64_t nrun, int parts, uint8_t *out_t,
+                                                          float *out_v, uint8_t *wave, float *pot) {
     extern __shared__ uint4 pwsm[];  // [splits][4 nq] findings
     __shared__ __align__(16) int bc[PW_LOC];
     __shared__ float bv[PW_LOC];
     __shared__ uint8_t bt[PW_LOC];
     const int tid = threadIdx.x;
-    const int part = blockIdx.x % parts, run = (blockIdx.x / parts) % nrun;
-    const int64_t b = blockIdx.x / parts / nrun;
-    const int p0 = run * PW_LOC, n = min(PW_LOC, HW - p0), nq = (n + 3) / 4;
+    const int part = blockIdx.x % parts;
+    const int64_t u = u0 + blockIdx.x / parts, b = u / nrun, p0 = (u - b * nrun) * PW_LOC;
+    const int n = (int)min<int64_t>(PW_LOC, HW - p0), nq = (n + 3) / 4;
     const int splits = min(min(PW_SPLITS, PW_THREADS / nq), C);
-    const int64_t plane = (int64_t)C * HW, base = b * plane + p0;
+    const int64_t plane = C * HW, base = b * plane + p0;
     PwBest *found = reinterpret_cast<PwBest *>(pwsm);
     if (tid < nq * splits) {
         const int sp = tid / nq, q = tid - sp * nq, nj = min(4, n - 4 * q);
@@ -85,14 +85,14 @@ __global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, con
             if (nj == 4) {
 #pragma unroll
                 for (int u = 0; u < PW_U; ++u) {  // (clamped: unconditional loads, all in flight)
-                    const int64_t o = base + (int64_t)min(c0 + u * splits, C - 1) * HW + 4 * q;
+                    const int64_t o = base + min(c0 + u * splits, C - 1) * HW + 4 * q;
                     tw[u] = reinterpret_cast<const Byte4u *>(tf + o)->w;
                     vw[u] = *reinterpret_cast<const Float4u *>(vf + o);
                 }
             } else {
 #pragma unroll
                 for (int u = 0; u < PW_U; ++u) {
-                    const int64_t o = base + (int64_t)min(c0 + u * splits, C - 1) * HW + 4 * q;
+                    const int64_t o = base + min(c0 + u * splits, C - 1) * HW + 4 * q;
                     tw[u] = 0;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, con
         const bool nan_first = p < n && a.first >= 0 && (a.first & 1);
         bc[p] = p < n ? (nan_first ? a.first >> 1 : a.c) : -1;
         bt[p] = (uint8_t)a.t;
-        bv[p] = nan_first ? vf[base + (int64_t)(a.first >> 1) * HW + p] : a.v;  // (its own bits)
+        bv[p] = nan_first ? vf[base + (a.first >> 1) * HW + p] : a.v;  // (its own bits)
     }
     __syncthreads();
     const int64_t items = (int64_t)C * nq, i1 = items * (part + 1) / parts;
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, con
         const int c = (int)(i / nq), q = (int)(i - (int64_t)c * nq), nj = min(4, n - 4 * q);
         const int4 w4 = *reinterpret_cast<const int4 *>(bc + 4 * q);
         const bool k[4] = {w4.x == c, w4.y == c, w4.z == c, w4.w == c};
-        const int64_t o = base + (int64_t)c * HW + 4 * q, ow = b * T * plane + p0 + (int64_t)c * HW + 4 * q;
+        const int64_t o = base + c * HW + 4 * q, ow = b * T * plane + p0 + c * HW + 4 * q;
         uint32_t tw = 0;
         Float4u v;
 #pragma unroll
@@ -254,7 +254,6 @@ extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_f
                 "spk_pointwise_inhibition: t_first, v_first, out_t_first and out_v_first are required");
     const int64_t HW = (int64_t)H * W, total = (int64_t)B * HW;
     SPK_REQUIRE(spk::ceil_div(total, 256) < (1LL << 31), SPK_E_RANGE, "spk_pointwise_inhibition: too large");
-    SPK_REQUIRE(HW < (1LL << 31) && (int64_t)C * HW < (1LL << 40), SPK_E_RANGE, "spk_pointwise_inhibition: too large");
     const int64_t nrun = spk::ceil_div(HW, PW_LOC);
     // more workgroups per run where the runs are few (each scans the run's inputs for
     // itself: 5 bytes a neuron, from L2 after the first), unless outputs are inputs
@@ -270,11 +269,13 @@ extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_f
                        on_inputs(potentials, 4 * T * N);
     const int64_t per_run = spk::ceil_div((int64_t)C * spk::ceil_div(std::min<int64_t>(HW, PW_LOC), 4), PW_THREADS);
     const int64_t parts = alias ? 1 : std::max<int64_t>(1, std::min<int64_t>({1024 / (B * nrun), 8, per_run}));
-    SPK_REQUIRE(B * nrun * parts < (1LL << 31), SPK_E_RANGE, "spk_pointwise_inhibition: too large");
     hipStream_t st = spk::as_stream(stream);
-    hipLaunchKernelGGL(k_pointwise, dim3((unsigned)(B * nrun * parts)), dim3(PW_THREADS),
-                       (size_t)PW_THREADS * 4 * sizeof(PwBest), st, t_first, v_first, T, C, (int)HW, (int)nrun,
-                       (int)parts, out_t_first, out_v_first, out_wave, potentials);
+    // a launch has fewer than 2^32 threads
+    const int64_t most = ((1LL << 32) - 1) / PW_THREADS / parts;
+    for (int64_t u0 = 0; u0 < B * nrun; u0 += most)
+        hipLaunchKernelGGL(k_pointwise, dim3((unsigned)(std::min(most, B * nrun - u0) * parts)), dim3(PW_THREADS),
+                           (size_t)PW_THREADS * 4 * sizeof(PwBest), st, t_first, v_first, T, C, HW, u0, nrun,
+                           (int)parts, out_t_first, out_v_first, out_wave, potentials);
     return spk::check_launch("spk_pointwise_inhibition");
 }
 

@@ -434,6 +434,25 @@ def test_pointwise_inhibition_runs(case, put):
     assert_equal(host(gp), rp, "masked potentials")
 
 
+def test_pointwise_inhibition_many_small_images():
+    # more images than one launch has workgroups of 512 threads (2^23): the result of 1009 distinct
+    # images, repeated
+    T, C, n, B = 5, 3, 1009, (1 << 23) + 700
+    g = synth.rng(735, 0)
+    tf = g.integers(0, T + 1, (n, C, 1, 1)).astype(np.uint8)
+    vf = (g.integers(0, 4, (n, C, 1, 1)) * 0.5).astype(np.float32)
+    rt, rv = orc.pointwise_inhibition(tf, vf, T)
+    reps = -(-B // n)
+
+    def many(a):
+        return dev(a).repeat(reps, 1, 1, 1)[:B].contiguous()
+
+    ot, ov, _ = spk.spk_pointwise_inhibition(many(tf), many(vf), T)
+    sync()
+    assert torch.equal(ot, many(rt)), "t_first"
+    assert torch.equal(ov, many(rv)), "v_first"
+
+
 @pytest.mark.parametrize("shape", [(2, 5, 27, 38), (1, 9, 40, 41), (3, 7, 1, 1)])
 def test_pointwise_inhibition_copies_the_winners_bits(shape):
     # a winner's potential is copied: one that is no number keeps its sign and payload
