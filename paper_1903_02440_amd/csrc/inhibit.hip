@@ -35,8 +35,8 @@ struct __attribute__((packed, aligned(4))) Float4u {
 // one when no output lies over an input, so the outputs may alias the inputs
 // (the first-spike ones, or at one step the wave and the potentials).
 // Bound by the writes (5 (1 + T) bytes a neuron with wave and potentials).  With
-// one thread per 4 locations doing all of it (the form before), 200 images of 250
-// maps of 14x14 kept 39 workgroups busy and read the potentials: 1444 us; now
+// one thread per 4 locations doing all of it (k_pointwise_each), 200 images of 250
+// maps of 14x14 keep 39 workgroups busy and read the potentials: 1444 us; this form
 // 245 us (833 MB, 3.4 TB/s).  256 or 1024 threads per workgroup 265 and 280 us;
 // items in the inner loop, steps in the outer one 280 us.
 //
@@ -60,19 +60,23 @@ __device__ __forceinline__ void pw_join(PwBest &a, int t, int c, int first, floa
     }
 }
 
-__global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, const float *vf, int T, int C, int64_t HW,
-                                                          int64_t u0, int64_t nrun, int parts, uint8_t *out_t,
-                                                          float *out_v, uint8_t *wave, float *pot) {
+// I holds the bytes of an image's potentials.
+template <typename I>
+__global__ __launch_bounds__(PW_THREADS, 4) void k_pointwise(const uint8_t *tf, const float *vf, int T, int C, I HW,
+                                                             int64_t u0, int64_t nrun, int parts, uint8_t *out_t,
+                                                             float *out_v, uint8_t *wave, float *pot) {
     extern __shared__ uint4 pwsm[];  // [splits][4 nq] findings
     __shared__ __align__(16) int bc[PW_LOC];
     __shared__ float bv[PW_LOC];
     __shared__ uint8_t bt[PW_LOC];
     const int tid = threadIdx.x;
     const int part = blockIdx.x % parts;
-    const int64_t u = u0 + blockIdx.x / parts, b = u / nrun, p0 = (u - b * nrun) * PW_LOC;
-    const int n = (int)min<int64_t>(PW_LOC, HW - p0), nq = (n + 3) / 4;
+    const int64_t u = u0 + blockIdx.x / parts, b = nrun == 1 ? u : u / nrun, p0 = (u - b * nrun) * PW_LOC;
+    const int n = (int)min<int64_t>(PW_LOC, (int64_t)HW - p0), nq = (n + 3) / 4;
     const int splits = min(min(PW_SPLITS, PW_THREADS / nq), C);
-    const int64_t plane = C * HW, base = b * plane + p0;
+    const int64_t plane = (int64_t)C * HW, base = b * plane + p0;
+    tf += base;
+    const char *vb = reinterpret_cast<const char *>(vf + base);
     PwBest *found = reinterpret_cast<PwBest *>(pwsm);
     if (tid < nq * splits) {
         const int sp = tid / nq, q = tid - sp * nq, nj = min(4, n - 4 * q);
@@ -85,19 +89,20 @@ __global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, con
             if (nj == 4) {
 #pragma unroll
                 for (int u = 0; u < PW_U; ++u) {  // (clamped: unconditional loads, all in flight)
-                    const int64_t o = base + min(c0 + u * splits, C - 1) * HW + 4 * q;
+                    const I o = (I)min(c0 + u * splits, C - 1) * HW + 4 * q;
                     tw[u] = reinterpret_cast<const Byte4u *>(tf + o)->w;
-                    vw[u] = *reinterpret_cast<const Float4u *>(vf + o);
+                    vw[u] = *reinterpret_cast<const Float4u *>(vb + 4 * o);
                 }
             } else {
 #pragma unroll
                 for (int u = 0; u < PW_U; ++u) {
-                    const int64_t o = base + min(c0 + u * splits, C - 1) * HW + 4 * q;
+                    const I o = (I)min(c0 + u * splits, C - 1) * HW + 4 * q;
                     tw[u] = 0;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        tw[u] |= (uint32_t)tf[o + min(j, nj - 1)] << (8 * j);
-                        vw[u].v[j] = vf[o + min(j, nj - 1)];
+                        const I oj = o + min(j, nj - 1);
+                        tw[u] |= (uint32_t)tf[oj] << (8 * j);
+                        vw[u].v[j] = *reinterpret_cast<const float *>(vb + 4 * oj);
                     }
                 }
             }
@@ -126,15 +131,17 @@ __global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, con
         const bool nan_first = p < n && a.first >= 0 && (a.first & 1);
         bc[p] = p < n ? (nan_first ? a.first >> 1 : a.c) : -1;
         bt[p] = (uint8_t)a.t;
-        bv[p] = nan_first ? vf[base + (a.first >> 1) * HW + p] : a.v;  // (its own bits)
+        bv[p] = nan_first ? *reinterpret_cast<const float *>(vb + 4 * ((I)(a.first >> 1) * HW + p)) : a.v;  // (its own bits)
     }
     __syncthreads();
-    const int64_t items = (int64_t)C * nq, i1 = items * (part + 1) / parts;
-    for (int64_t i = items * part / parts + tid; i < i1; i += PW_THREADS) {
-        const int c = (int)(i / nq), q = (int)(i - (int64_t)c * nq), nj = min(4, n - 4 * q);
+    // items (feature, 4 locations) of the part's features, PW_THREADS on each time
+    const int c1 = (int)((int64_t)C * (part + 1) / parts), cs = PW_THREADS / nq, qs = PW_THREADS - cs * nq;
+    int c = (int)((int64_t)C * part / parts) + tid / nq, q = tid % nq;
+    for (; c < c1; c += cs + (q + qs >= nq ? 1 : 0), q = q + qs >= nq ? q + qs - nq : q + qs) {
+        const int nj = min(4, n - 4 * q);
         const int4 w4 = *reinterpret_cast<const int4 *>(bc + 4 * q);
         const bool k[4] = {w4.x == c, w4.y == c, w4.z == c, w4.w == c};
-        const int64_t o = base + c * HW + 4 * q, ow = b * T * plane + p0 + c * HW + 4 * q;
+        const int64_t e = (I)c * HW + 4 * q, o = base + e, ow = b * T * plane + p0 + e;
         uint32_t tw = 0;
         Float4u v;
 #pragma unroll
@@ -178,6 +185,133 @@ __global__ __launch_bounds__(PW_THREADS) void k_pointwise(const uint8_t *tf, con
             }
         }
     }
+}
+
+// One thread per location of one image (VEC: per 4 consecutive locations,
+// with 4-byte / 16-byte accesses; the map size is then a multiple of 4): the
+// winner over the C features, then every feature's surviving first-spike time
+// and potential, and, when asked, the survivors' Eq.1 wave and the masked
+// potentials.  All C features of the locations are read before any is written,
+// so the outputs may alias the inputs.  Consecutive threads take consecutive
+// locations, so every per-feature access of a wave is contiguous.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_pointwise_each(const uint8_t *tf, const float *vf, int64_t B, int T, int C,
+                                                        int64_t HW, uint8_t *out_t, float *out_v, uint8_t *wave,
+                                                        float *pot) {
+    constexpr int L = VEC ? 4 : 1;
+    const int64_t per_img = HW / L;
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= B * per_img) return;
+    const int64_t b = q / per_img, p = (q - b * per_img) * L;
+    const int64_t base = b * C * HW + p;
+    int best[L], bt[L];
+    float bv[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+        best[j] = -1;
+        bt[j] = T;
+        bv[j] = 0.0f;
+    }
+    // features in blocks of PW_U, every load of a block issued before the
+    // first is used (clamped feature indices keep them unconditional), in
+    // increasing feature order so that strict comparisons keep the lower index
+    for (int c0 = 0; c0 < C; c0 += PW_U) {
+        uint32_t tw[PW_U];
+        float4 vw[PW_U];
+#pragma unroll
+        for (int u = 0; u < PW_U; ++u) {
+            const int64_t o = base + (int64_t)min(c0 + u, C - 1) * HW;
+            if (VEC) {
+                tw[u] = *reinterpret_cast<const uint32_t *>(tf + o);
+                vw[u] = *reinterpret_cast<const float4 *>(vf + o);
+            } else {
+                tw[u] = tf[o];
+                vw[u].x = vf[o];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PW_U; ++u) {
+            const int c = c0 + u;
+            if (c >= C) break;
+            int t[L];
+            float v[L];
+            t[0] = tw[u] & 255u;
+            v[0] = vw[u].x;
+            if (VEC) {
+                t[L > 1 ? 1 : 0] = (tw[u] >> 8) & 255u;
+                t[L > 2 ? 2 : 0] = (tw[u] >> 16) & 255u;
+                t[L > 3 ? 3 : 0] = tw[u] >> 24;
+                v[L > 1 ? 1 : 0] = vw[u].y; v[L > 2 ? 2 : 0] = vw[u].z; v[L > 3 ? 3 : 0] = vw[u].w;
+            }
+#pragma unroll
+            for (int j = 0; j < L; ++j)
+                if (t[j] < T && (best[j] < 0 || t[j] < bt[j] || (t[j] == bt[j] && v[j] > bv[j]))) {
+                    best[j] = c;
+                    bt[j] = t[j];
+                    bv[j] = v[j];
+                }
+        }
+    }
+    // the surviving first-spike times of feature c, 4 to a word
+    auto word = [&](int c) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int j = 0; j < L; ++j) w |= (uint32_t)(c == best[j] ? bt[j] : T) << (8 * j);
+        return w;
+    };
+    for (int c = 0; c < C; ++c) {
+        if (VEC) {
+            *reinterpret_cast<uint32_t *>(out_t + base + c * HW) = word(c);
+            *reinterpret_cast<float4 *>(out_v + base + c * HW) =
+                float4{c == best[0] ? bv[0] : 0.0f, c == best[L > 1 ? 1 : 0] ? bv[L > 1 ? 1 : 0] : 0.0f,
+                       c == best[L > 2 ? 2 : 0] ? bv[L > 2 ? 2 : 0] : 0.0f,
+                       c == best[L > 3 ? 3 : 0] ? bv[L > 3 ? 3 : 0] : 0.0f};
+        } else {
+            out_t[base + c * HW] = (uint8_t)(c == best[0] ? bt[0] : T);
+            out_v[base + c * HW] = c == best[0] ? bv[0] : 0.0f;
+        }
+    }
+    const int64_t plane = (int64_t)C * HW;
+    if (wave)  // feature by feature: its surviving times once, then its T steps
+        for (int c = 0; c < C; ++c) {
+            uint8_t *w = wave + b * T * plane + (int64_t)c * HW + p;
+            if (VEC) {
+                const uint32_t wc = word(c);
+                for (int t = 0; t < T; ++t) *reinterpret_cast<uint32_t *>(w + t * plane) = spk::spikes4(wc, t, T);
+            } else {
+                const int tc = c == best[0] ? bt[0] : T;
+                for (int t = 0; t < T; ++t) w[t * plane] = (uint8_t)(t >= tc);
+            }
+        }
+    if (pot)
+        for (int t = 0; t < T; ++t) {
+            float *pp = pot + (b * T + t) * plane + p;
+            if constexpr (VEC) {
+                // blocks of PW_U features: the loads first (clamped), then the masked stores
+                for (int c0 = 0; c0 < C; c0 += PW_U) {
+                    float4 xw[PW_U];
+#pragma unroll
+                    for (int u = 0; u < PW_U; ++u)
+                        xw[u] = *reinterpret_cast<const float4 *>(pp + (int64_t)min(c0 + u, C - 1) * HW);
+#pragma unroll
+                    for (int u = 0; u < PW_U; ++u) {
+                        const int c = c0 + u;
+                        if (c >= C) break;
+                        if (c == best[0] && c == best[1] && c == best[2] && c == best[3])
+                            continue;  // the feature survives at all four locations
+                        float4 x = xw[u];
+                        if (c != best[0]) x.x = 0.0f;
+                        if (c != best[1]) x.y = 0.0f;
+                        if (c != best[2]) x.z = 0.0f;
+                        if (c != best[3]) x.w = 0.0f;
+                        *reinterpret_cast<float4 *>(pp + (int64_t)c * HW) = x;
+                    }
+                }
+            } else {
+                for (int c = 0; c < C; ++c)
+                    if (c != best[0]) pp[c * HW] = 0.0f;
+            }
+        }
 }
 
 // One thread per output value: the maximum over the window of the zero-padded
@@ -242,6 +376,23 @@ __global__ __launch_bounds__(256) void k_pool_potentials_2x2_even(const float *_
     out[i] = m;
 }
 
+// Whether one thread per location does better than a workgroup per run.  That form
+// takes about 0.3 us a feature (a quad of locations per thread; 0.15 one at a time) until
+// the locations fill the chip, and T times that with the wave or the potentials; the
+// workgroups share the features of a location, as far as its run leaves them threads,
+// but are as many as there are images, however little each has to do.  Measured at
+// T = 15 (each : runs, us): first spikes of 250 maps of 14x14, 200 images 91 : 81,
+// 1000 images 135 : 162; of 28x28, 8 images 84 : 114; 30 maps of 28x28, 200 images
+// 16 : 45; 200 of 4x4, 1000 images 73 : 30, 4096 77 : 107; 150 of 7x9, 64 images 25 : 20,
+// 256 28 : 37.  With wave and potentials 64 maps of 14x14, 1000 images 507 : 363; 8 of
+// 64x64, 16 images 36 : 24, 128 109 : 163; 12 of 7x7, 1000 images 20 : 28; 4 of 9x9, 100
+// images 7.5 : 8.7; 10 of 1x1, 1000 images 42 : 10, 100,000 147 : 818.
+bool pw_each(int64_t B, int C, int64_t HW, int64_t nrun, bool vec, bool steps) {
+    const int64_t loc = B * HW;
+    if (steps) return C < 8 || loc > (vec ? 262144 : 40000) || B * nrun > std::max(4096, 64 * C);
+    return C < (vec ? 32 : 100) || HW > 448 || loc > (vec ? std::max(12800, 200 * C) : 50 * C) || B > 2048;
+}
+
 }  // namespace
 
 extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_first, int B, int T, int C, int H,
@@ -254,7 +405,20 @@ extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_f
                 "spk_pointwise_inhibition: t_first, v_first, out_t_first and out_v_first are required");
     const int64_t HW = (int64_t)H * W, total = (int64_t)B * HW;
     SPK_REQUIRE(spk::ceil_div(total, 256) < (1LL << 31), SPK_E_RANGE, "spk_pointwise_inhibition: too large");
+    auto al = [](const void *q, uintptr_t a) { return ((uintptr_t)q & (a - 1)) == 0; };
+    const bool vec = HW % 4 == 0 && al(t_first, 4) && al(out_t_first, 4) && al(out_wave, 4) && al(v_first, 16) &&
+                     al(out_v_first, 16) && al(potentials, 16);
+    hipStream_t st = spk::as_stream(stream);
     const int64_t nrun = spk::ceil_div(HW, PW_LOC);
+    if (pw_each(B, C, HW, nrun, vec, out_wave || potentials)) {
+        if (vec)
+            hipLaunchKernelGGL(k_pointwise_each<true>, dim3((unsigned)spk::ceil_div(total / 4, 256)), dim3(256), 0, st,
+                               t_first, v_first, (int64_t)B, T, C, HW, out_t_first, out_v_first, out_wave, potentials);
+        else
+            hipLaunchKernelGGL(k_pointwise_each<false>, dim3((unsigned)spk::ceil_div(total, 256)), dim3(256), 0, st,
+                               t_first, v_first, (int64_t)B, T, C, HW, out_t_first, out_v_first, out_wave, potentials);
+        return spk::check_launch("spk_pointwise_inhibition");
+    }
     // more workgroups per run where the runs are few (each scans the run's inputs for
     // itself: 5 bytes a neuron, from L2 after the first), unless outputs are inputs
     const int64_t N = (int64_t)B * C * HW;
@@ -268,14 +432,19 @@ extern "C" int spk_pointwise_inhibition(const uint8_t *t_first, const float *v_f
     const bool alias = on_inputs(out_t_first, N) || on_inputs(out_v_first, 4 * N) || on_inputs(out_wave, T * N) ||
                        on_inputs(potentials, 4 * T * N);
     const int64_t per_run = spk::ceil_div((int64_t)C * spk::ceil_div(std::min<int64_t>(HW, PW_LOC), 4), PW_THREADS);
-    const int64_t parts = alias ? 1 : std::max<int64_t>(1, std::min<int64_t>({1024 / (B * nrun), 8, per_run}));
-    hipStream_t st = spk::as_stream(stream);
+    const int64_t parts = alias ? 1 : std::max<int64_t>(1, std::min<int64_t>({1024 / (B * nrun), 8, per_run, C}));
     // a launch has fewer than 2^32 threads
     const int64_t most = ((1LL << 32) - 1) / PW_THREADS / parts;
-    for (int64_t u0 = 0; u0 < B * nrun; u0 += most)
-        hipLaunchKernelGGL(k_pointwise, dim3((unsigned)(std::min(most, B * nrun - u0) * parts)), dim3(PW_THREADS),
-                           (size_t)PW_THREADS * 4 * sizeof(PwBest), st, t_first, v_first, T, C, HW, u0, nrun,
-                           (int)parts, out_t_first, out_v_first, out_wave, potentials);
+    for (int64_t u0 = 0; u0 < B * nrun; u0 += most) {
+        const dim3 grid((unsigned)(std::min(most, B * nrun - u0) * parts));
+        const size_t lds = (size_t)PW_THREADS * 4 * sizeof(PwBest);
+        if (C * HW <= 1LL << 30)
+            hipLaunchKernelGGL(k_pointwise<uint32_t>, grid, dim3(PW_THREADS), lds, st, t_first, v_first, T, C,
+                               (uint32_t)HW, u0, nrun, (int)parts, out_t_first, out_v_first, out_wave, potentials);
+        else
+            hipLaunchKernelGGL(k_pointwise<uint64_t>, grid, dim3(PW_THREADS), lds, st, t_first, v_first, T, C,
+                               (uint64_t)HW, u0, nrun, (int)parts, out_t_first, out_v_first, out_wave, potentials);
+    }
     return spk::check_launch("spk_pointwise_inhibition");
 }
 

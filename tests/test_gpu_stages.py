@@ -434,6 +434,34 @@ def test_pointwise_inhibition_runs(case, put):
     assert_equal(host(gp), rp, "masked potentials")
 
 
+# Both forms, on both sides of the rule between them: one thread per location (few features, many
+# or large maps) and workgroups that share a run's features (many features, few small maps); with
+# the wave and the potentials the workgroups take larger maps too
+@pytest.mark.parametrize("case", [(2, 31, 14, 14), (2, 32, 14, 14), (65, 64, 14, 14), (66, 64, 14, 14),
+                                  (1, 40, 20, 22), (1, 40, 20, 23), (1, 100, 7, 9), (80, 100, 7, 9),
+                                  (2049, 40, 2, 2), (3, 7, 16, 16), (3, 8, 16, 16), (26, 8, 39, 41),
+                                  (4097, 9, 2, 2)])
+@pytest.mark.parametrize("put", [dev, dev_shifted])
+def test_pointwise_inhibition_forms(case, put):
+    B, C, H, W = case
+    T = 4
+    g = synth.rng(760 + C + H, 0)
+    tf = g.integers(0, T + 1, case).astype(np.uint8)
+    vf = (g.integers(0, 5, case) * 0.5).astype(np.float32)
+    pot = g.normal(0, 3, (B, T, C, H, W)).astype(np.float32)
+    rt, rv, rp = orc.pointwise_inhibition(tf, vf, T, pot)
+    gp, it, iv = put(pot), put(tf), put(vf)
+    first = spk.spk_pointwise_inhibition(it, iv, T)
+    steps = spk.spk_pointwise_inhibition(it, iv, T, out_wave=None, potentials=gp)
+    spk.spk_pointwise_inhibition(it, iv, T, out_t_first=it, out_v_first=iv)
+    sync()
+    for what, (t, v) in (("first spikes", first[:2]), ("with steps", steps[:2]), ("in place", (it, iv))):
+        assert_equal(host(t), rt, "t_first, " + what)
+        assert_equal(host(v), rv, "v_first, " + what)
+    assert_equal(host(steps[2]), orc.expand_wave(rt, T), "wave")
+    assert_equal(host(gp), rp, "masked potentials")
+
+
 def test_pointwise_inhibition_many_small_images():
     # more images than one launch has workgroups of 512 threads (2^23): the result of 1009 distinct
     # images, repeated
