@@ -5,10 +5,11 @@
 // window; zero padding) and Eq.3 for the output size, read as
 // floor((H + 2D - P)/R) + 1 (equal to the printed form whenever P == R).
 //
-// One thread per output neuron (b, c, yo, xo) of the wave form: for every
-// step t it ORs the window's bytes of plane t and stores one byte, so a wave
-// reads and writes consecutive x positions of one plane; the first-spike map
-// is T minus the number of steps at which the pooled neuron is on.
+// Waves, in the general form, take one thread per output neuron (b, c, yo, xo):
+// for every step t it ORs the window's bytes of plane t and stores one byte, so a
+// wave reads and writes consecutive x positions of one plane; the first-spike map
+// is T minus the number of steps at which the pooled neuron is on.  Larger batches
+// of maps that fit go through LDS.
 #include <algorithm>
 #include <cstdint>
 
@@ -368,7 +369,17 @@ extern "C" int spk_pool(const uint8_t *wave, int B, int T, int C, int H, int W, 
     if (HW <= WL_BYTES && hw <= WL_QUADS * 1024 && Ho < 1024 && Wo < 1024) {  // whole maps through LDS
         const int CB = (int)std::min<int64_t>({(int64_t)C, WL_BYTES / HW, WL_QUADS * 1024 / hw, (int64_t)2047});
         const int64_t blocks = (int64_t)B * spk::ceil_div(C, CB);
-        if (blocks < (1LL << 31)) {
+        // Its workgroups are few and walk all steps with two barriers each: it pays once they
+        // are about as many as the CUs, with 2x2 and 3x3 windows of whole maps; the other windows'
+        // loops are slower and need twice that, large ones more.  Measured at T = 15 (an output per
+        // thread : LDS, us): 30 maps of 28x28, 2x2, 16 images (48 workgroups) 9.7 : 11.5, 64 (192) 15.1 : 12.0;
+        // 250 of 14x14, 3x3, 16 images (64) 14.8 : 23.4, 64 (256) 33 : 24; 64 of 64x64, 2x2, 4
+        // images (128) 12.2 : 13.0, 8 (256) 20.5 : 13.3; 32 of 64x64, 5x5, 16 images (128)
+        // 40 : 73, 64 (512) 84 : 77; 30 of 28x28, 3x3 stride 2 padded, 64 images (192) 27 : 72,
+        // 256 (768) 112 : 79; 4 of 100x120, 7x7 stride 6, T = 30, 128 images (512) 207 : 249,
+        // 256 (1024) 343 : 255.  (A launch has fewer than 2^32 threads.)
+        const bool few_taps = pad == 0 && (kernel == 2 || kernel == 3);
+        if (blocks >= (few_taps ? 192 : kernel <= 5 ? 512 : 640) && blocks < (1LL << 24)) {
 #define SPK_POOL_WAVE(PW, IN)                                                                                          \
     hipLaunchKernelGGL((k_pool_lds<PW, IN>), dim3((unsigned)blocks), dim3(256), 0, spk::as_stream(stream), wave, T, C, \
                        H, W, kernel, stride, pad, Ho, Wo, CB, out_wave, out_t_first)

@@ -359,6 +359,18 @@ def test_pool_parity(case):
     assert_equal(host(so), ref, "pooled wave, unaligned")
 
 
+# Batches from which waves go through LDS (192 workgroups of 2x2 or 3x3 windows, 512 of others, 640 from 6x6
+# on) and the ones just below: a map a workgroup or all maps of an image, ragged quads, maps that end
+# in the last bytes, padding, more outputs than inputs, T > 127
+@pytest.mark.parametrize("case", [(191, 3, 37, 13, 11, 3, 3, 0), (192, 3, 37, 13, 11, 3, 3, 0),
+                                  (192, 3, 130, 3, 5, 2, 2, 0), (97, 5, 30, 28, 28, 2, 2, 0),
+                                  (171, 3, 3, 127, 129, 5, 4, 2), (170, 3, 3, 127, 129, 5, 4, 2),
+                                  (512, 200, 2, 6, 7, 2, 1, 1), (511, 3, 5, 6, 7, 2, 1, 1),
+                                  (512, 3, 8, 12, 12, 4, 2, 1), (640, 2, 5, 19, 21, 7, 6, 0)])
+def test_pool_parity_batches(case):
+    test_pool_parity(case)
+
+
 @pytest.mark.parametrize("case", POOL_CASES)
 def test_pool_first_spike_parity(case):
     B, T, C, H, W, P, R, D = case
