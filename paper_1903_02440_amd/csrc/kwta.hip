@@ -393,18 +393,29 @@ __global__ __launch_bounds__(TOPK_THREADS_SMALL_B) void k_kwta_topk(const uint8_
 // same input have their maxima at the same places, so one winner inhibits the
 // maximum of every map; with runs of maps it inhibits those of the runs at its
 // place only.  Runs of all maps would suffer in the opposite case, a feature
-// that is the best almost everywhere.  Hence at most UN_MAX units with about as
-// many positions as maps to a side: 256 maps of 256x256 make 256 x 16 units of
-// 256 positions x 16 maps, 20 KB to read again.
+// that is the best almost everywhere.  Hence runs of UN_MAPS maps, which one wave
+// reads at once, longer where that makes more than UN_MAX units: 256 maps of
+// 256x256 make 256 x 16 units of 256 positions x 16 maps, 20 KB to read again; 250
+// of 14x14 make 4 x 32 units of 64 positions x 8 maps.
 // Bound by the one pass over the maps (5 bytes a neuron) and k rounds of two
 // reductions each.  With the maxima of tiles of 16 rows, all of them read again
 // whose maximum was inhibited, 4 images of 256 maps of 256x256, k = 32, took
 // 14.6 ms; now 0.48 ms, 79 us of it the pass (4.3 TB/s) and the rest the
-// latency of the rounds' reads (5 to 14 us a round).
+// latency of the rounds' reads (5 to 14 us a round).  Smaller maps whose features
+// spike at the same places, k = 32, 32 images: 250 of 14x14 176 us with the maxima
+// of tiles, 429 with runs of one map, 163 so; 256 of 64x64 1770, 2540 and 592 (runs
+// of 4 maps 1013, of 16 698).
 constexpr int UN_MAX = 4096;      // units per image at most (8 bytes each in the workspace)
 constexpr int UN_UPT = 4;         // units per thread of the rounds
 constexpr int UN_THREADS = UN_MAX / UN_UPT;
-constexpr int UN_WIDE = 4096;     // positions from which a lane takes 4 (fewer groups), else 1
+// Few waves wait longer for what a round reads again, many for each other at its
+// barriers (250 maps of 14x14, one image, k = 32, shared places: 4 waves 267 us, 8 167,
+// 16 162; independent ones 99, 78, 97).
+constexpr int UN_MIN_THREADS = 512;
+// Units of 64 positions up to here, of 256 beyond: narrow ones are less to read again, but
+// more to hold (32 images, k = 32, shared places, 64 : 256 positions: 30 maps of 64x64 118 :
+// 154 us, 20 of 90x90 84 : 102).
+constexpr int UN_NARROW = 1024;
 constexpr int UN_MAPS = 8;        // maps a wave reads at once
 constexpr int UN_MAX_C = 4096;    // feature maps at most (the retired ones' bitmap)
 
@@ -445,11 +456,25 @@ __device__ __forceinline__ uint64_t unit_best(const uint8_t *__restrict__ tf, co
     if (inh && ok) ok &= ~(inh[p >> 5] >> (p & 31));
     uint64_t m = 0;
     for (int f0 = fa; f0 < fb; f0 += U) {
+        // the block's live maps (uniform), then the last of them again in place of the others
+        uint32_t live = (1u << min(U, fb - f0)) - 1u;
+        if (dead) {
+            const uint64_t d = (uint64_t)dead[(f0 >> 5) + 1] << 32 | dead[f0 >> 5];
+            live &= ~(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(d >> (f0 & 31)));
+        }
+        if (live == 0) continue;
+        int fq[U];
+        const int n = __popc(live);
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            fq[q] = f0 + __ffs((int)live) - 1;
+            live = live & (live - 1) ? live & (live - 1) : live;
+        }
         uint32_t tw[U];  // L first-spike times, a byte each
         float vv[U][L];
 #pragma unroll
-        for (int q = 0; q < U; ++q) {  // (clamped: unconditional loads, all in flight)
-            const int o = min(f0 + q, fb - 1) * g.HW;
+        for (int q = 0; q < U; ++q) {  // (unconditional loads, all in flight)
+            const int o = fq[q] * g.HW;
             if (L == 4 && g.vec) {     // (whole quads: HW is a multiple of 4)
                 const int oq = o + min(p, g.HW - 4);
                 tw[q] = *reinterpret_cast<const uint32_t *>(tf + oq);
@@ -470,8 +495,8 @@ __device__ __forceinline__ uint64_t unit_best(const uint8_t *__restrict__ tf, co
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int f = f0 + q;
-            if (f >= fb || (dead && ((dead[f >> 5] >> (f & 31)) & 1u))) continue;  // uniform
+            const int f = fq[q];
+            if (q >= n) continue;  // uniform
 #pragma unroll
             for (int j = 0; j < L; ++j) {
                 const int t = (int)((tw[q] >> (8 * j)) & 255u);
@@ -505,7 +530,7 @@ __global__ __launch_bounds__(UN_THREADS) void k_kwta_rounds(const uint8_t *__res
                                                             int32_t *__restrict__ winners,
                                                             int32_t *__restrict__ n_winners) {
     extern __shared__ uint32_t inh[];         // bitmap of the inhibited positions
-    __shared__ uint32_t dead[UN_MAX_C / 32];  // bitmap of the retired features
+    __shared__ uint32_t dead[UN_MAX_C / 32 + 1];  // bitmap of the retired features
     __shared__ uint64_t red[2][UN_THREADS / 64];
     __shared__ uint64_t res[UN_MAX];          // the listed units' new keys
     __shared__ uint16_t list[UN_MAX];
@@ -517,7 +542,7 @@ __global__ __launch_bounds__(UN_THREADS) void k_kwta_rounds(const uint8_t *__res
     const float *vf = vf_all + b * N;
     int32_t *win = winners + (int64_t)b * g.k * 4;
     for (int i = tid; i < nwords; i += NT) inh[i] = 0;
-    for (int i = tid; i < UN_MAX_C / 32; i += NT) dead[i] = 0;
+    for (int i = tid; i < UN_MAX_C / 32 + 1; i += NT) dead[i] = 0;
     for (int i = tid; i < 4 * g.k; i += NT) win[i] = -1;
     uint64_t K[UN_UPT];
 #pragma unroll
@@ -529,7 +554,8 @@ __global__ __launch_bounds__(UN_THREADS) void k_kwta_rounds(const uint8_t *__res
     if (tid == 0) nlist = 0;
     __syncthreads();
     int found = 0;
-    for (int round = 0; round < g.k; ++round) {
+    const int rounds = min(g.k, g.C);  // (each retires a feature)
+    for (int round = 0; round < rounds; ++round) {
         bool valid[UN_UPT];
         uint64_t m = 0;
 #pragma unroll
@@ -604,9 +630,9 @@ __global__ __launch_bounds__(UN_THREADS) void k_kwta_rounds(const uint8_t *__res
 KwtaUnits kwta_units(int B, int T, int C, int H, int W, int k, int r) {
     KwtaUnits g{};
     g.B = B; g.T = T; g.C = C; g.HW = H * W; g.W = W; g.k = k; g.r = r;
-    g.L = g.HW >= UN_WIDE ? 4 : 1;
+    g.L = (g.HW + 63) / 64 * ((C + UN_MAPS - 1) / UN_MAPS) > UN_NARROW ? 4 : 1;
     g.groups = (int)spk::ceil_div(g.HW, 64 * g.L);  // at most 256
-    const int ns = std::min(C, UN_MAX / g.groups);
+    const int ns = std::min((C + UN_MAPS - 1) / UN_MAPS, UN_MAX / g.groups);
     g.fps = (C + ns - 1) / ns;
     g.ns = (C + g.fps - 1) / g.fps;
     g.units = g.ns * g.groups;
@@ -734,7 +760,8 @@ extern "C" int spk_kwta(const uint8_t *t_first, const float *v_first, int B, int
     const int64_t blocks = (int64_t)B * ((g.units + 3) / 4);
     SPK_REQUIRE(blocks < (1LL << 31), SPK_E_RANGE, "spk_kwta: batch too large");
     hipLaunchKernelGGL(k_kwta_units, dim3((unsigned)blocks), dim3(256), 0, st, t_first, v_first, g);
-    const int nt = (int)std::min<int64_t>(UN_THREADS, spk::align_up((size_t)g.units, 64));
+    const int nt = (int)std::max<int64_t>(g.L == 1 && g.ns >= 24 ? UN_THREADS : UN_MIN_THREADS,
+                                          spk::align_up((size_t)spk::ceil_div(g.units, UN_UPT), 64));
     const size_t lds = (size_t)(g.HW + 31) / 32 * 4;
     if (g.L == 4)
         hipLaunchKernelGGL(k_kwta_rounds<4>, dim3(B), dim3(nt), lds, st, t_first, v_first, g, winners, n_winners);

@@ -638,6 +638,25 @@ def test_kwta_units(case, kind):
         assert_equal(host(win), rw, "winners")
 
 
+# Runs of 7 maps, whose retired ones lie in two words of the bitmap; more rounds than maps; a last
+# run of one map; runs of 9 maps, read in two parts (256 groups of positions); fewer units than
+# waves; shared places, so that one winner's window invalidates all runs
+@pytest.mark.parametrize("case", [(2, 6, 33, 20, 20, 40, 0), (3, 5, 9, 9, 9, 17, 1), (1, 8, 130, 256, 256, 20, 3),
+                                  (2, 15, 250, 14, 14, 20, 1), (1, 15, 512, 7, 7, 20, 0), (9, 7, 17, 64, 64, 25, 2)])
+def test_kwta_units_runs(case):
+    B, T, C, H, W, k, r = case
+    g = synth.rng(880 + C + H, 0)
+    place = g.integers(0, T + 3, (B, 1, H, W))
+    tf = np.minimum(place + (g.random((B, C, H, W)) < 0.2), T).astype(np.uint8)
+    vf = (g.integers(0, 7, (B, C, H, W)) * 0.5).astype(np.float32)
+    vf[tf >= T] = 0
+    win, nw = spk.spk_kwta(dev(tf), dev(vf), T, k, r)
+    sync()
+    rwin, rnw = orc.kwta(tf, vf, T, k, r)
+    assert_equal(host(nw), rnw, "n_winners")
+    assert_equal(host(win), rwin, "winners")
+
+
 def test_kwta_toy_t3_and_silent(golden):
     g = golden("t3_kwta.txt")
     T = int(g["T"][0])
