@@ -510,12 +510,12 @@ __device__ __forceinline__ uint64_t unit_best(const uint8_t *__restrict__ tf, co
     return wave_max_u64_dpp(m);
 }
 
-// Grid: image * ceil(units / 4) blocks of 4 units, one wave each.  Consecutive
-// units are the runs of maps at one place.
+// Grid: image (from b0 on) * ceil(units / 4) blocks of 4 units, one wave each.
+// Consecutive units are the runs of maps at one place.
 __global__ __launch_bounds__(256) void k_kwta_units(const uint8_t *__restrict__ tf, const float *__restrict__ vf,
-                                                    KwtaUnits g) {
-    const int nblk = (g.units + 3) / 4, lane = threadIdx.x & 63;
-    const int b = blockIdx.x / nblk, u = (int)(blockIdx.x - b * nblk) * 4 + (int)(threadIdx.x >> 6);
+                                                    KwtaUnits g, int b0) {
+    const int nblk = (g.units + 3) / 4, lane = threadIdx.x & 63, bi = blockIdx.x / nblk;
+    const int b = b0 + bi, u = (int)(blockIdx.x - bi * nblk) * 4 + (int)(threadIdx.x >> 6);
     if (u >= g.units) return;
     const int64_t N = (int64_t)g.C * g.HW;
     const int grp = u / g.ns, fa = (u - grp * g.ns) * g.fps, fb = min(g.C, fa + g.fps);
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(256) void k_kwta_units(const uint8_t *__restrict__ 
 
 template <int L>
 __global__ __launch_bounds__(UN_THREADS) void k_kwta_rounds(const uint8_t *__restrict__ tf_all,
-                                                            const float *__restrict__ vf_all, KwtaUnits g,
+                                                            const float *__restrict__ vf_all, KwtaUnits g, int b0,
                                                             int32_t *__restrict__ winners,
                                                             int32_t *__restrict__ n_winners) {
     extern __shared__ uint32_t inh[];         // bitmap of the inhibited positions
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(UN_THREADS) void k_kwta_rounds(const uint8_t *__res
     __shared__ uint64_t res[UN_MAX];          // the listed units' new keys
     __shared__ uint16_t list[UN_MAX];
     __shared__ int nlist;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int b = b0 + (int)blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int NT = blockDim.x, NW = NT >> 6, nwords = (g.HW + 31) / 32;
     const int64_t N = (int64_t)g.C * g.HW;
     const uint8_t *tf = tf_all + b * N;
@@ -716,7 +716,9 @@ int kwta_check(int B, int T, int C, int H, int W, int k, int r) {
     SPK_REQUIRE((int64_t)H * W <= 65536, SPK_E_RANGE, "spk_kwta: H*W > 65536");
     SPK_REQUIRE(k >= 1 && r >= 0, SPK_E_ARG, "spk_kwta: k=%d must be >= 1 and radius=%d >= 0", k, r);
     SPK_REQUIRE(C <= UN_MAX_C, SPK_E_RANGE, "spk_kwta: %d feature maps exceed %d", C, UN_MAX_C);
-    // the batch limit of the call: B * (tiles of RB rows) * (lanes up to 64 that cover one) < 2^31
+    // The batch limit of the call, kept as it is whatever the kernels' launches need (they stay below
+    // it): with maps cut into tiles of RB rows so that an image has at most UN_MAX, and G lanes, up to
+    // 64, that cover a tile, fewer than 2^31 lanes in all.
     int RB = 1, G = 1;
     while (RB < H && (int64_t)C * ((H + RB - 1) / RB) > UN_MAX) RB *= 2;
     RB = std::min(RB, H);
@@ -757,15 +759,22 @@ extern "C" int spk_kwta(const uint8_t *t_first, const float *v_first, int B, int
     KwtaUnits g = kwta_units(B, T, C, H, W, k, radius);
     g.ukey = static_cast<uint64_t *>(workspace);
     g.vec = g.L == 4 && g.HW % 4 == 0 && ((uintptr_t)t_first & 3) == 0 && ((uintptr_t)v_first & 15) == 0;
-    const int64_t blocks = (int64_t)B * ((g.units + 3) / 4);
-    SPK_REQUIRE(blocks < (1LL << 31), SPK_E_RANGE, "spk_kwta: batch too large");
-    hipLaunchKernelGGL(k_kwta_units, dim3((unsigned)blocks), dim3(256), 0, st, t_first, v_first, g);
+    const int nblk = (g.units + 3) / 4, most = ((1 << 24) - 1) / nblk;  // a launch has fewer than 2^32 threads
+    for (int64_t b0 = 0; b0 < B; b0 += most)
+        hipLaunchKernelGGL(k_kwta_units, dim3((unsigned)(std::min<int64_t>(most, B - b0) * nblk)), dim3(256), 0, st,
+                           t_first, v_first, g, (int)b0);
     const int nt = (int)std::max<int64_t>(g.L == 1 && g.ns >= 24 ? UN_THREADS : UN_MIN_THREADS,
                                           spk::align_up((size_t)spk::ceil_div(g.units, UN_UPT), 64));
     const size_t lds = (size_t)(g.HW + 31) / 32 * 4;
-    if (g.L == 4)
-        hipLaunchKernelGGL(k_kwta_rounds<4>, dim3(B), dim3(nt), lds, st, t_first, v_first, g, winners, n_winners);
-    else
-        hipLaunchKernelGGL(k_kwta_rounds<1>, dim3(B), dim3(nt), lds, st, t_first, v_first, g, winners, n_winners);
+    const int64_t imgs = ((1LL << 32) - 1) / nt;
+    for (int64_t b0 = 0; b0 < B; b0 += imgs) {
+        const dim3 grid((unsigned)std::min<int64_t>(imgs, B - b0));
+        if (g.L == 4)
+            hipLaunchKernelGGL(k_kwta_rounds<4>, grid, dim3(nt), lds, st, t_first, v_first, g, (int)b0, winners,
+                               n_winners);
+        else
+            hipLaunchKernelGGL(k_kwta_rounds<1>, grid, dim3(nt), lds, st, t_first, v_first, g, (int)b0, winners,
+                               n_winners);
+    }
     return spk::check_launch("spk_kwta");
 }

@@ -657,6 +657,24 @@ def test_kwta_units_runs(case):
     assert_equal(host(win), rwin, "winners")
 
 
+@pytest.mark.parametrize("B,C", [((1 << 23) + 700, 2), ((1 << 17) + 5, 4096)])
+def test_kwta_units_many_small_images(B, C):
+    # more images than one launch holds workgroups of 512 threads (2^23 of 2 neurons) or of 4 units
+    # (2^24, 128 an image): the winners of 503 distinct images, repeated
+    T, k, n = 4, 17, 503
+    tf, vf = kwta_inputs(C, n, T, C, 1, 1, True)
+    reps = -(-B // n)
+
+    def many(a):
+        return dev(a).repeat((reps,) + (1,) * (a.ndim - 1))[:B].contiguous()
+
+    win, nw = spk.spk_kwta(many(tf), many(vf), T, k, 0)
+    sync()
+    rw, rn = orc.kwta(tf, vf, T, k, 0)
+    assert torch.equal(nw, many(rn)), "n_winners"
+    assert torch.equal(win, many(rw)), "winners"
+
+
 def test_kwta_toy_t3_and_silent(golden):
     g = golden("t3_kwta.txt")
     T = int(g["T"][0])
