@@ -353,19 +353,19 @@ __global__ __launch_bounds__(256) void k_rank_collect(const float *__restrict__ 
     }
 }
 
-// Grid (boundary, image): the workgroup of a digit's first boundary finds the
+// Grid (boundary, image from b0 on): the workgroup of a digit's first boundary finds the
 // keys of all boundaries in that digit.  Segments of at most RK_LDS keys go
 // into LDS: a second digit (the next 10 float bits) by histogram, then the
 // entries with the boundaries' second digits, at most RK_SUB of them, ranked
 // directly (the number of larger keys).  Longer segments, or many equal
 // values, take an MSD radix select over the rest of the key, 8 bits a pass.
-__global__ __launch_bounds__(256) void k_rank_resolve(int64_t N, int T, RankWork w) {
+__global__ __launch_bounds__(256) void k_rank_resolve(int64_t N, int T, RankWork w, int b0) {
     __shared__ uint64_t lk[RK_LDS];      // keys; the digit passes' histograms [RK_GROUPS][256]
     __shared__ uint64_t sub[RK_SUB];     // keys with the boundaries' second digits; the passes' prefixes
     __shared__ uint32_t hist[1025];      // second digits: entries with digit >= d
     __shared__ uint32_t mark[32], trank[RK_T], wsum[4];
     __shared__ int tsub[RK_T], s_m, s_ng;
-    const int j0 = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int j0 = blockIdx.x, b = b0 + (int)blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int4 *tg = w.targ + (int64_t)b * RK_T + j0;
     const int4 t0 = tg[0];
     const int nt = t0.w, cnt = t0.y;
@@ -1689,7 +1689,9 @@ void launch_rank(const float *I, int B, int64_t N, int T, uint8_t *t_first, uint
         hipLaunchKernelGGL(k_rank_select, dim3(B), dim3(1024), 0, st, T, w);
         const int cc = (int)std::min<int64_t>(spk::ceil_div(N, RK_CHUNK), 4096);
         hipLaunchKernelGGL(k_rank_collect, dim3((unsigned)(B * cc)), dim3(256), 0, st, I, N, cc, w);
-        hipLaunchKernelGGL(k_rank_resolve, dim3((unsigned)(T - 1), (unsigned)B), dim3(256), 0, st, N, T, w);
+        for (int64_t b0 = 0; b0 < B; b0 += 65535)  // (the grid's second side)
+            hipLaunchKernelGGL(k_rank_resolve, dim3((unsigned)(T - 1), (unsigned)std::min<int64_t>(65535, B - b0)),
+                               dim3(256), 0, st, N, T, w, (int)b0);
     }
     const int chunks = (int)std::max<int64_t>(1, std::min<int64_t>(1024, spk::ceil_div(N, 16 * 256)));
     hipLaunchKernelGGL(k_expand_latency, dim3((unsigned)(B * chunks)), dim3(256), 0, st, I, N, T, w.bounds, t_first,

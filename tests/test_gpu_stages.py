@@ -824,6 +824,18 @@ def test_rank_latency_parity(shape, T):
     assert_equal(host(wave), orc.expand_wave(rtf, T), "wave")
 
 
+def test_rank_latency_more_images_than_a_grid_side():
+    # 65535 workgroups are a grid's second side: 66000 images of just more than 8192 entries, 40 of
+    # them distinct
+    B, n, T = 66000, 40, 5
+    g = synth.rng(957, 0)
+    x = g.normal(0, 40, (n, 1, 1, 8196)).astype(np.float32)
+    rtf = orc.rank_latency(x, T)
+    _, tf = spk.spk_rank_latency(dev(x).repeat(B // n, 1, 1, 1), T, wave=False)
+    sync()
+    assert torch.equal(tf, dev(rtf).repeat(B // n, 1, 1, 1)), "t_first"
+
+
 # Maps of more than 8192 entries: many workgroups per image.  A first digit's segment is resolved
 # in LDS up to 4096 keys and 1024 with the boundaries' second digits, else by digit passes; the
 # last entries of an image are no whole 16; up to 254 boundaries, in one digit or one per digit.
