@@ -1752,7 +1752,9 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
     SPK_REQUIRE(filter_lds(R) <= 65536, SPK_E_RANGE, "spk_encode_latency: %d filters of %dx%d on width %d do not fit",
                 C, KF, KF, W);
     bool counted = false;
-    if (C <= MAX_DERIV_C) {
+    const int ntx = (W + FT_W - 1) / FT_W, nty = (H + FT_H - 1) / FT_H;
+    // (a launch has fewer than 2^32 threads: very many narrow images take bands, which are fewer)
+    if (C <= MAX_DERIV_C && (int64_t)B * ntx * nty < (1LL << 24)) {
         // the digits are counted while they are made when 16-bit counters hold a tile's entries
         const bool rank = (t_first || wave) && p.N > SMALL_MAX && T > 1;
         counted = rank && C * FT_H * FT_W < 65536;
@@ -1761,7 +1763,6 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
         const size_t itaps_lds = up16((size_t)C * ((KF + 1) / 2) * KF * sizeof(uint32_t));
         hipLaunchKernelGGL(k_enc_prepare, dim3(clear_blocks(words)), dim3(ENC_THREADS), taps_lds + itaps_lds, st,
                            filters, C, KF, bank, rw.hist, words);
-        const int ntx = (W + FT_W - 1) / FT_W, nty = (H + FT_H - 1) / FT_H;
         const size_t lds = up16((size_t)(FT_H + KF - 1) * small_filter_wp(FT_W, KF) * sizeof(uint32_t)) +
                            (counted ? RK_BINS / 2 * sizeof(uint32_t) : 0) + std::max(taps_lds, itaps_lds);
         hipLaunchKernelGGL(k_filter_tile, dim3((unsigned)((int64_t)B * ntx * nty)), dim3(ENC_THREADS), lds, st, image,

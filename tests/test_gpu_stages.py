@@ -801,6 +801,19 @@ def test_encode_few_images_stay_in_their_buffers(B, H, W):
     assert (host(room[B:]) == -7.0).all(), "intensities past the batch were written"
 
 
+def test_encode_more_tiles_than_a_launch_has_workgroups():
+    # 2^24 tiles of 32x64: narrow images, which are filtered by bands then; 64 distinct ones, repeated
+    B, n, H = (1 << 18) + 64, 64, 2048
+    g = synth.rng(462, 0)
+    img = g.integers(0, 256, (n, H, 1)).astype(np.uint8)
+    bank = (g.integers(-64, 65, (1, 3, 3)) / 64.0).astype(np.float32)
+    _, _, inten = spk.spk_encode_latency(dev(img).repeat(B // n, 1, 1), dev(bank), 5, wave=False, t_first=False,
+                                         intensities=None)
+    sync()
+    I, _, _ = orc.encode(img, bank, 5, 0.0)
+    assert torch.equal(inten, dev(I).repeat(B // n, 1, 1, 1)), "intensities"
+
+
 @pytest.mark.parametrize("r,shape", [(0, (3, 6, 28, 28)), (2, (3, 6, 28, 28)), (8, (3, 6, 28, 28)),
                                      (30, (3, 6, 28, 28)), (8, (1, 2, 100, 250)), (3, (2, 1, 37, 5))])
 def test_local_normalization_parity(r, shape):
