@@ -188,7 +188,7 @@ constexpr int RK_BINS = 1 << 13;
 constexpr int RK_T = 256;             // table rows per image (at most 254 boundaries)
 constexpr int RK_CHUNK = 4096;        // entries a workgroup takes at a time (16 per thread)
 constexpr int RK_LDS = 4096;          // keys of one digit resolved in LDS
-constexpr int RK_SUB = 1024;          // ... and of its second digits that hold boundaries
+constexpr int RK_SUB = 384;           // ... and of its second digits that hold boundaries, ranked directly
 constexpr int RK_GROUPS = 32;         // boundaries resolved at once by the digit passes
 constexpr int RK_HIST_MAX = 60 * 1024;  // entries a workgroup counts at most (16-bit counters)
 
@@ -358,13 +358,20 @@ __global__ __launch_bounds__(256) void k_rank_collect(const float *__restrict__ 
 // into LDS: a second digit (the next 10 float bits) by histogram, then the
 // entries with the boundaries' second digits, at most RK_SUB of them, ranked
 // directly (the number of larger keys).  Longer segments, or many equal
-// values, take an MSD radix select over the rest of the key, 8 bits a pass.
+// values, take an MSD radix select over the rest of the key, 8 bits a pass,
+// without the digits that are the same in the whole segment (equal values have
+// only the index's left); a wave whose keys all have one digit counts it with
+// one addition.  The whole code, T = 20, one select workgroup per image : these
+// passes without either : now: 64 images of 160,000 equal entries 1260 : 1680 to
+// 2370 : 1030 us; 256 of 9600 entries of ten values 96 : 413 : 78, the most from up
+// to 1024 equal keys ranked directly (RK_SUB).
 __global__ __launch_bounds__(256) void k_rank_resolve(int64_t N, int T, RankWork w, int b0) {
     __shared__ uint64_t lk[RK_LDS];      // keys; the digit passes' histograms [RK_GROUPS][256]
     __shared__ uint64_t sub[RK_SUB];     // keys with the boundaries' second digits; the passes' prefixes
     __shared__ uint32_t hist[1025];      // second digits: entries with digit >= d
     __shared__ uint32_t mark[32], trank[RK_T], wsum[4];
     __shared__ int tsub[RK_T], s_m, s_ng;
+    __shared__ uint64_t s_diff[4];
     const int j0 = blockIdx.x, b = b0 + (int)blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int4 *tg = w.targ + (int64_t)b * RK_T + j0;
     const int4 t0 = tg[0];
@@ -372,15 +379,28 @@ __global__ __launch_bounds__(256) void k_rank_resolve(int64_t N, int T, RankWork
     if (nt == 0) return;  // (uniform)
     const uint64_t *L = w.list + (int64_t)b * N + t0.x;
     uint64_t *bounds = w.bounds + (int64_t)b * (T - 1) + j0;
-    if (cnt <= RK_LDS) {
-        for (int i0 = tid; i0 < cnt; i0 += 4 * 256) {
-            uint64_t v[4];
+    uint64_t key0 = 0, diff = 0;  // more than RK_SUB keys: the first, and the bits in which others differ from it
+    if (cnt > RK_SUB) {
+        key0 = L[0];
+        for (int i0 = tid; i0 < cnt; i0 += 8 * 256) {
+            uint64_t v[8];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = L[min(i0 + k * 256, cnt - 1)];
+            for (int k = 0; k < 8; ++k) v[k] = L[min(i0 + k * 256, cnt - 1)];
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (i0 + k * 256 < cnt) lk[i0 + k * 256] = v[k];
+            for (int k = 0; k < 8; ++k) {
+                diff |= v[k] ^ key0;
+                if (cnt <= RK_LDS && i0 + k * 256 < cnt) lk[i0 + k * 256] = v[k];
+            }
         }
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) diff |= __shfl_xor((unsigned long long)diff, s, 64);
+        if (lane == 0) s_diff[wv] = diff;
+        __syncthreads();
+        diff = s_diff[0] | s_diff[1] | s_diff[2] | s_diff[3];
+    }
+    // (one second digit for more than RK_SUB keys: nothing to be had here)
+    if (cnt <= RK_SUB || (cnt <= RK_LDS && ((diff >> 40) & 1023u) != 0)) {
+        for (int i = tid; i < (cnt <= RK_SUB ? cnt : 0); i += 256) lk[i] = L[i];
         for (int i = tid; i < 1024; i += 256) hist[i] = 0;
         if (tid < 32) mark[tid] = 0;
         if (tid == 0) s_m = 0;
@@ -451,10 +471,15 @@ __global__ __launch_bounds__(256) void k_rank_resolve(int64_t N, int T, RankWork
         const int m = min(RK_GROUPS, nt - q0);
         if (tid < m) {
             trank[tid] = (uint32_t)tg[q0 + tid].z;
-            tpre[tid] = L[0] >> 56;
+            tpre[tid] = key0 >> 56;
         }
         __syncthreads();
         for (int shift = 48; shift >= 0; shift -= 8) {
+            if (((diff >> shift) & 255u) == 0) {  // (uniform) the same digit everywhere
+                if (tid < m) tpre[tid] = (tpre[tid] << 8) | ((key0 >> shift) & 255u);
+                __syncthreads();
+                continue;
+            }
             if (tid == 0) {  // the distinct prefixes (non-increasing in j)
                 int g = -1;
                 for (int j = 0; j < m; ++j) {
@@ -467,24 +492,36 @@ __global__ __launch_bounds__(256) void k_rank_resolve(int64_t N, int T, RankWork
             const int ng = s_ng;
             for (int i = tid; i < ng * 256; i += 256) (&gh[0][0])[i] = 0;
             __syncthreads();
-            for (int i0 = tid; i0 < cnt; i0 += 4 * 256) {
-                uint64_t v[4];
+            for (int i0 = tid; i0 < cnt; i0 += 8 * 256) {
+                uint64_t v[8];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) v[k] = L[min(i0 + k * 256, cnt - 1)];
+                for (int k = 0; k < 8; ++k) v[k] = L[min(i0 + k * 256, cnt - 1)];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if (i0 + k * 256 >= cnt) break;
-                    const uint64_t pk = v[k] >> (shift + 8);
-                    int lo = 0, hi = ng - 1;  // gpre is descending
-                    while (lo <= hi) {
-                        const int mid = (lo + hi) >> 1;
-                        const uint64_t gp = gpre[mid];
-                        if (gp == pk) {
-                            atomicAdd(&gh[mid][(uint32_t)(v[k] >> shift) & 255u], 1u);
-                            break;
+                for (int k = 0; k < 8; ++k) {
+                    int at = -1;  // group and digit
+                    if (i0 + k * 256 < cnt) {
+                        const uint64_t pk = v[k] >> (shift + 8);
+                        int lo = 0, hi = ng - 1;  // gpre is descending
+                        while (lo <= hi) {
+                            const int mid = (lo + hi) >> 1;
+                            const uint64_t gp = gpre[mid];
+                            if (gp == pk) {
+                                at = mid << 8 | (int)((v[k] >> shift) & 255u);
+                                break;
+                            }
+                            if (gp > pk) lo = mid + 1;
+                            else hi = mid - 1;
                         }
-                        if (gp > pk) lo = mid + 1;
-                        else hi = mid - 1;
+                    }
+                    const uint64_t in = __ballot(at >= 0);
+                    if (at >= 0) {
+                        const int a0 = __builtin_amdgcn_readfirstlane(at);
+                        if (__ballot(at == a0) == in) {
+                            if (lane == __ffsll((unsigned long long)in) - 1)
+                                atomicAdd(&gh[0][0] + a0, (uint32_t)__popcll(in));
+                        } else {
+                            atomicAdd(&gh[0][0] + at, 1u);
+                        }
                     }
                 }
             }

@@ -837,6 +837,26 @@ def test_rank_latency_parity(shape, T):
     assert_equal(host(wave), orc.expand_wave(rtf, T), "wave")
 
 
+@pytest.mark.parametrize("run", [1, 383, 384, 385, 4096, 4097, 40000])
+@pytest.mark.parametrize("spread", [0, 1, 300])
+def test_rank_latency_ties_at_the_boundary(run, spread):
+    # T = 4: two boundaries inside a run of entries that are equal, or of `spread` neighbouring floats
+    # with the same second digit (bits 17..8), at random places; direct ranks up to 384 keys, then digit
+    # passes without the digits that are the same everywhere, in LDS' reach up to 4096 and past it
+    N = 4 * run + 8200
+    g = synth.rng(958 + spread, run)
+    x = np.empty(N, np.float32)
+    lo = N // 4 - run // 4  # larger values before the run
+    x[:lo] = 4.0 + g.random(lo, dtype=np.float32) * 100
+    x[lo:lo + run] = (np.float32(1.5).view(np.uint32) + (g.integers(0, spread, run) % 256 if spread else 0)).astype(
+        np.uint32).view(np.float32)
+    x[lo + run:] = g.random(N - lo - run, dtype=np.float32) * np.float32(0.9)
+    x = x[g.permutation(N)].reshape(1, 1, 1, N)
+    _, tf = spk.spk_rank_latency(dev(x), 4, wave=False)
+    sync()
+    assert_equal(host(tf), orc.rank_latency(x, 4), "t_first")
+
+
 def test_rank_latency_more_images_than_a_grid_side():
     # 65535 workgroups are a grid's second side: 66000 images of just more than 8192 entries, 40 of
     # them distinct
@@ -850,7 +870,7 @@ def test_rank_latency_more_images_than_a_grid_side():
 
 
 # Maps of more than 8192 entries: many workgroups per image.  A first digit's segment is resolved
-# in LDS up to 4096 keys and 1024 with the boundaries' second digits, else by digit passes; the
+# in LDS up to 4096 keys and 384 with the boundaries' second digits, else by digit passes; the
 # last entries of an image are no whole 16; up to 254 boundaries, in one digit or one per digit.
 RANK_LARGE = [("floats", (2, 4, 60, 61), 30), ("floats", (1, 1, 97, 173), 255), ("flat", (2, 4, 60, 61), 30),
               ("flat", (1, 3, 53, 53), 255), ("few", (2, 4, 60, 61), 15), ("few", (1, 6, 91, 93), 255),
