@@ -788,11 +788,27 @@ def test_encode_parity(case):
 
 @pytest.mark.parametrize("B,H,W", [(2, 160, 250), (2, 156, 286), (3, 100, 120)])
 def test_encode_few_images_stay_in_their_buffers(B, H, W):
-    # few images: the filter's bands are cut thinner than LDS asks for, and a height that they
-    # do not divide must not leave workgroups for images past the batch
+    # few images by tiles: the last ones of a side are cut short, and none lies past the batch
     g = synth.rng(460, H)
     img, bank = synth.pink_noise_images(g, B, H, W), synth.gabor_bank()
     room = torch.full((3 * B, 4, H, W), -7.0, dtype=torch.float32, device="cuda")
+    _, tf, inten = spk.spk_encode_latency(dev(img), dev(bank), 15, wave=False, intensities=room[:B])
+    sync()
+    I, rtf, _ = orc.encode(img, bank, 15, 0.0)
+    assert_equal(host(inten), I, "intensities")
+    assert_equal(host(tf), rtf, "t_first")
+    assert (host(room[B:]) == -7.0).all(), "intensities past the batch were written"
+
+
+@pytest.mark.parametrize("B,C,H,W", [(2, 65, 160, 30), (2, 70, 101, 22), (3, 65, 100, 40)])
+def test_encode_few_images_by_bands_stay_in_their_buffers(B, C, H, W):
+    # more than 64 channels are filtered by bands of rows, cut thinner for few images: heights that
+    # the bands do not divide (160 rows and 64 bands asked for: 54 of 3 rows) must not leave
+    # workgroups for images past the batch
+    g = synth.rng(463, C + H)
+    img = g.integers(0, 256, (B, H, W)).astype(np.uint8)
+    bank = (g.integers(-64, 65, (C, 3, 3)) / 64.0).astype(np.float32)
+    room = torch.full((3 * B, C, H, W), -7.0, dtype=torch.float32, device="cuda")
     _, tf, inten = spk.spk_encode_latency(dev(img), dev(bank), 15, wave=False, intensities=room[:B])
     sync()
     I, rtf, _ = orc.encode(img, bank, 15, 0.0)
