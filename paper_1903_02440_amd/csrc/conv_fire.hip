@@ -1813,9 +1813,9 @@ __global__ __launch_bounds__((INF_WAVES + INF_ZW) * 64, 1) void k_conv_fire_inf(
                 if (kl >= nk) break;  // uniform
                 uint4 bt[NT][INF_NW];
 #pragma unroll
-                for (int n = 0; n < INF_NW; ++n)
+                for (int q = 0; q < NT; ++q)
 #pragma unroll
-                    for (int q = 0; q < NT; ++q) bt[q][n] = fr[((kl * INF_NW + n) * NT + q) * 64];
+                    for (int n = 0; n < INF_NW; ++n) bt[q][n] = fr[((kl * INF_NW + n) * NT + q) * 64];
                 u4 a[INF_MW];
 #pragma unroll
                 for (int i = 0; i < INF_MW; ++i) {
@@ -1830,6 +1830,23 @@ __global__ __launch_bounds__((INF_WAVES + INF_ZW) * 64, 1) void k_conv_fire_inf(
                     for (int i = 0; i < INF_MW; ++i)
 #pragma unroll
                         for (int n = 0; n < INF_NW; ++n) acc[i][n] = mfma<KIND>(a[i], bt[q][n], acc[i][n]);
+                // the first operand is formed while the first term's reads are under way, the
+                // second one between products of the first, and the second term is read between
+                // products of the second one
+                __builtin_amdgcn_sched_group_barrier(0x100, INF_NW, 0);  // LDS reads
+                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);       // VALU
+#pragma unroll
+                for (int n = 0; n < INF_NW - 1; ++n) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                }
+#pragma unroll
+                for (int n = 0; n < INF_NW - 1; ++n) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
         };
         if constexpr (pm) {
