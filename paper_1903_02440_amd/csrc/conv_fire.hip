@@ -1189,8 +1189,8 @@ __global__ __launch_bounds__(FIN_THREADS, 1) void k_conv_fire_fin(
 // smallest that do not fit run as fast here, those of 13 K-steps 20 % slower).
 // A workgroup of TG groups of 4 waves makes NP = 64 * MT positions of the
 // flattened (image, position) space times 16 * NTL features for all steps; a wave
-// holds MT position tiles x NTL feature tiles x STR_TB steps of accumulators, the
-// groups of waves consecutive runs of STR_TB steps.  The fragments of KC K-steps
+// holds MT position tiles x NTL feature tiles x TB steps of accumulators, the
+// groups of waves consecutive runs of TB steps.  The fragments of KC K-steps
 // at a time go through two LDS buffers, shared by all waves: the transfers of the
 // next chunk are issued right after the barrier that hands over the current one
 // and are waited for at the next, a whole chunk of products later.  The rows of
@@ -1205,7 +1205,6 @@ __global__ __launch_bounds__(FIN_THREADS, 1) void k_conv_fire_fin(
 // stores, which other waves cover.  With each wave reading the fragments from L2
 // for itself (8 times the traffic, one K-step ahead) it took 12.5 ms, and 31
 // 65x43 maps of 13 channels, 70 features of 7x7, stride 2: 399 us, now 202.
-constexpr int STR_TB = 3;
 __host__ __device__ constexpr int str_kc(int MT, int NTL) { return MT * NTL >= 8 ? 2 : 4; }
 __host__ __device__ constexpr int str_chunk_u4(int MT, int NTL) { return str_kc(MT, NTL) * NTL * NT * 64; }
 __host__ __device__ constexpr int str_stage(int MT) { return 32 * (64 * MT + 4); }  // floats
@@ -1226,13 +1225,13 @@ __device__ __forceinline__ void str_landed(uint32_t (&w)[KC][MT][2]) {
         for (int i = 0; i < MT; ++i) asm volatile("" : "+v"(w[k][i][0]), "+v"(w[k][i][1]));
 }
 
-template <int MT, int NTL, int TG, bool ALDS>
+template <int MT, int NTL, int TG, int TB, bool ALDS>
 __global__ __launch_bounds__(256 * TG, 2) void k_conv_fire_str(
     const uint8_t *__restrict__ tpad, const uint4 *__restrict__ frag, const int2 *__restrict__ koff2, ConvGeom g,
     int n_fg, int n_chunks, const float *__restrict__ inv_scale, const int *__restrict__ wbf16, float *__restrict__ P,
     uint8_t *__restrict__ S, uint8_t *__restrict__ TF, float *__restrict__ VF) {
     constexpr int KC = str_kc(MT, NTL), CHUNK = str_chunk_u4(MT, NTL), NP = 64 * MT, SP = NP + 4;
-    constexpr int TB = STR_TB, THREADS = 256 * TG;
+    constexpr int THREADS = 256 * TG;
     constexpr int GPW = KC * NTL * NT / (4 * TG);  // 1 KB transfers per wave and chunk
     extern __shared__ uint4 lds[];
     uint4 *ring = lds;                                               // [2][CHUNK]
@@ -2222,7 +2221,7 @@ int64_t rows_of_positions(const ConvGeom &g, int cpos) {
     return R * g.S + g.K + d * std::max(0, g.Hp - g.Ho * g.S);
 }
 
-template <int MT, int NTL, int TG>
+template <int MT, int NTL, int TG, int TB>
 void launch_str(const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const float *inv_scale, const int *wbf16,
                 const ConvGeom &g, float *P, uint8_t *S, uint8_t *TF, float *VF, hipStream_t st) {
     const int n_fg = (int)spk::ceil_div(g.Cout, 16 * NTL);
@@ -2232,10 +2231,10 @@ void launch_str(const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const
     const size_t rows = (size_t)rows_of_positions(g, 64 * MT) * g.Wp * g.CP;
     const size_t with = str_lds(MT, NTL, g.ksteps, spk::align_up(rows, 16));
     if (with <= (TG == 4 ? 160 : 80) * 1024)
-        hipLaunchKernelGGL((k_conv_fire_str<MT, NTL, TG, true>), grid, dim3(256 * TG), with, st, tpad, frag, koff2, g,
+        hipLaunchKernelGGL((k_conv_fire_str<MT, NTL, TG, TB, true>), grid, dim3(256 * TG), with, st, tpad, frag, koff2, g,
                            n_fg, n_chunks, inv_scale, wbf16, P, S, TF, VF);
     else
-        hipLaunchKernelGGL((k_conv_fire_str<MT, NTL, TG, false>), grid, dim3(256 * TG), str_lds(MT, NTL, g.ksteps, 0),
+        hipLaunchKernelGGL((k_conv_fire_str<MT, NTL, TG, TB, false>), grid, dim3(256 * TG), str_lds(MT, NTL, g.ksteps, 0),
                            st, tpad, frag, koff2, g, n_fg, n_chunks, inv_scale, wbf16, P, S, TF, VF);
 }
 
@@ -2494,16 +2493,34 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
         // images of the natural layer: 321 against 326 us a step), as far as there are steps.
         const int64_t np64 = spk::ceil_div(npos, 64);
         const int fg4 = (int)spk::ceil_div(Cout, 64), fg2 = (int)spk::ceil_div(Cout, 32);
-#define SPK_STR(MT, NTL, TG) \
-    launch_str<MT, NTL, TG>(tpad, frag, koff2, inv_scale, wbf16, g, potentials, spikes, t_first, v_first, st)
+#define SPK_STR(MT, NTL, TG, TB) \
+    launch_str<MT, NTL, TG, TB>(tpad, frag, koff2, inv_scale, wbf16, g, potentials, spikes, t_first, v_first, st)
+        // Steps a wave takes at a time: those of 3, 4 and 5 with the fewest steps computed past T,
+        // of equals the most (fewer passes over the fragments).  T = 15 with 3 by two groups
+        // computes 18, with 4 16: 8 images of 16 64x64 maps, 64 features of 7x7, 135 : 122 us, of
+        // 32 maps and 5x5 135 : 121; with the fragments read from L2 by every wave, 5 steps at a
+        // time, 122 and 122 (but 240 for 96 maps and 3x3, with unaligned maps 1.8 times as much as
+        // here, and 107 : 112 with 8 maps and 9x9, where a step has only 21 products).
+        auto steps_of = [&](int tg) {
+            int best = 5;
+            for (int tb = 4; tb >= 3; --tb)
+                if (spk::ceil_div(T, tg * tb) * tb < spk::ceil_div(T, tg * best) * best) best = tb;
+            return best;
+        };
+        const int tb2 = steps_of(2), tb4 = steps_of(4);
         if (2 * fg4 == fg2 && np64 / 2 * fg4 >= 512)
-            SPK_STR(2, 4, 1);
-        else if (T <= STR_TB)
-            SPK_STR(1, 2, 1);
-        else if (np64 * fg2 > 256 || T <= 2 * STR_TB)
-            SPK_STR(1, 2, 2);
-        else
-            SPK_STR(1, 2, 4);
+            SPK_STR(2, 4, 1, 3);
+        else if (T <= 3)
+            SPK_STR(1, 2, 1, 3);
+        else if (np64 * fg2 > 256 || T <= 6) {
+            if (tb2 == 3) SPK_STR(1, 2, 2, 3);
+            else if (tb2 == 4) SPK_STR(1, 2, 2, 4);
+            else SPK_STR(1, 2, 2, 5);
+        } else {
+            if (tb4 == 3) SPK_STR(1, 2, 4, 3);
+            else if (tb4 == 4) SPK_STR(1, 2, 4, 4);
+            else SPK_STR(1, 2, 4, 5);
+        }
 #undef SPK_STR
     } else {
 #define SPK_FIN(G, BL, AL)                                                                                          \

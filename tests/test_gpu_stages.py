@@ -161,6 +161,23 @@ def fin_task_form(B, Cout, Ho, Wo):
     return ("image", (mt & 3) in (1, 2) and mt > 8 and ct == 16)
 
 
+# The steps a wave takes at a time: 3, 4 or 5 by T, with two or four groups of waves
+STREAM_STEP_CASES = [
+    ("two-groups-of-5-steps", 90, 10, 4, 26, 41, 20, 17, 0, 1, 36.0, 0.5),
+    ("two-groups-of-5-steps-words-from-L2", 14, 9, 160, 26, 25, 33, 5, 2, 1, 60.0, 0.6),
+    ("two-groups-of-4-steps-words-from-L2", 14, 8, 160, 26, 25, 33, 5, 2, 1, 60.0, 0.6),
+    ("four-groups-of-3-steps", 3, 11, 4, 26, 41, 20, 17, 0, 1, 36.0, 0.5),
+    ("four-groups-of-3-steps-words-from-L2", 1, 9, 160, 26, 25, 33, 5, 2, 1, 60.0, 0.6),
+    ("four-groups-of-5-steps-words-from-L2", 1, 18, 160, 26, 25, 33, 5, 2, 1, 60.0, 0.6),
+]
+
+
+@pytest.mark.parametrize("case", STREAM_STEP_CASES, ids=[c[0] for c in STREAM_STEP_CASES])
+@pytest.mark.parametrize("kind", ["normal", "dyadic"])
+def test_conv_fire_streamed_steps(case, kind, near_log):
+    test_conv_fire_streamed_weights(case, kind, near_log)
+
+
 def test_split_cases_take_the_whole_image_split():
     for name in ("tiles9-split", "tiles10-split", "tiles13-split", "tiles14-split"):
         _, B, T, Cin, H, W, Cout, K, pad, thr, ps = next(c for c in CONV_CASES if c[0] == name)
