@@ -2226,7 +2226,7 @@ void launch_str(const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const
                 const ConvGeom &g, float *P, uint8_t *S, uint8_t *TF, float *VF, hipStream_t st) {
     const int n_fg = (int)spk::ceil_div(g.Cout, 16 * NTL);
     const int n_chunks = (int)spk::ceil_div((int64_t)g.B * g.HoWo, 64 * MT);
-    const dim3 grid((unsigned)((n_chunks + 7) / 8 * n_fg * 8));
+    const dim3 grid((unsigned)((int64_t)(n_chunks + 7) / 8 * n_fg * 8));
     // the rows in LDS when two workgroups per CU still fit, else the words from L2
     const size_t rows = (size_t)rows_of_positions(g, 64 * MT) * g.Wp * g.CP;
     const size_t with = str_lds(MT, NTL, g.ksteps, spk::align_up(rows, 16));
@@ -2508,7 +2508,9 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
             return best;
         };
         const int tb2 = steps_of(2), tb4 = steps_of(4);
-        if (2 * fg4 == fg2 && np64 / 2 * fg4 >= 512)
+        // (a launch has fewer than 2^32 threads; the larger groups need a quarter as many)
+        const bool fits = spk::align_up((size_t)np64, 8) * fg2 * (T <= 3 ? 256 : 512) < (1ULL << 32);
+        if (!fits || (2 * fg4 == fg2 && np64 / 2 * fg4 >= 512))
             SPK_STR(2, 4, 1, 3);
         else if (T <= 3)
             SPK_STR(1, 2, 1, 3);

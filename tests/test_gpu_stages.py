@@ -172,6 +172,23 @@ STREAM_STEP_CASES = [
 ]
 
 
+def test_conv_fire_streamed_more_positions_than_a_launch_has_threads():
+    # 8200 maps of 256x256 are more than 2^29 positions, in groups of 64 by 512 threads each more
+    # threads than a launch may have: 41 distinct images, repeated
+    n, reps, T, K = 41, 200, 4, 17
+    g = synth.rng(192, 0)
+    tf = synth.times_uniform_or_silent(g, (n, 1, 256, 256), T, 0.6)
+    Wt = synth.dyadic_weights(g, (1, 1, K, K), K * K)
+    _, _, gt, gv = spk.spk_conv_fire_first_spike(dev(tf).repeat(reps, 1, 1, 1), T, dev(Wt), 8, 20.0,
+                                                 potentials=False, spikes=False)
+    sync()
+    _, _, rt, rv = orc.conv_fire(wave_of(tf[:3], T), Wt, 8, 20.0)
+    assert_equal(host(gt[:3]), rt, "t_first")
+    assert_equal(host(gv[:3]), rv, "v_first")
+    for r in range(1, reps):
+        assert torch.equal(gt[r * n:(r + 1) * n], gt[:n]) and torch.equal(gv[r * n:(r + 1) * n], gv[:n]), r
+
+
 @pytest.mark.parametrize("case", STREAM_STEP_CASES, ids=[c[0] for c in STREAM_STEP_CASES])
 @pytest.mark.parametrize("kind", ["normal", "dyadic"])
 def test_conv_fire_streamed_steps(case, kind, near_log):
