@@ -1199,10 +1199,10 @@ __global__ __launch_bounds__(FIN_THREADS, 1) void k_conv_fire_fin(
 // steps the accumulators go through LDS, 32 features of a step at a time, so that
 // P and S leave as runs of NP positions; first spikes are written when they happen
 // (steps in order, one bit per neuron remembers them).
-// Bound by the matrix cores where K is large: the layer of 64 256x256 maps, 256
-// features of 5x5, T = 64 takes 5.0 ms (1.4 PFLOP/s in two 16-bit terms; a large
-// bf16 matrix product reaches 1.23 here), elsewhere by the latency of the staged
-// stores, which other waves cover.  With each wave reading the fragments from L2
+// Near the matrix cores where K is large: the layer of 64 256x256 maps, 256
+// features of 5x5, T = 64 takes 5.0 to 5.2 ms (1.4 PFLOP/s in two 16-bit terms, 55 %
+// of the nominal dense 2.5; a large bf16 matrix product of the library reaches 1.23
+// here), elsewhere bound by the latency of the staged stores, which other waves cover.  With each wave reading the fragments from L2
 // for itself (8 times the traffic, one K-step ahead) it took 12.5 ms, and 31
 // 65x43 maps of 13 channels, 70 features of 7x7, stride 2: 399 us, now 202.
 __host__ __device__ constexpr int str_kc(int MT, int NTL) { return MT * NTL >= 8 ? 2 : 4; }
@@ -2193,9 +2193,9 @@ void launch_fin(const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const
 }
 
 // The form of a call: fp32, fused pooling, or plain (whose weights are in LDS:
-// those that do not fit are streamed).
+// those that do not fit are streamed, by another kernel; false: no such form).
 template <int G, bool BLDS, bool ALDS>
-void launch_fin_form(bool pooled, const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const float *inv_scale,
+bool launch_fin_form(bool pooled, const uint8_t *tpad, const uint4 *frag, const int2 *koff2, const float *inv_scale,
                      const int *wbf16, const float *wts, const unsigned *wmax, const unsigned *wmin, int n_wmax,
                      const ConvGeom &g, int n_pairs, int n_chunks, int cpi, int chunk_tiles, int band_pos, int np_max,
                      int a_words, size_t lds, float *P, uint8_t *S, uint8_t *TF, float *VF, const PoolOut &po,
@@ -2211,6 +2211,9 @@ void launch_fin_form(bool pooled, const uint8_t *tpad, const uint4 *frag, const 
         launch(std::integral_constant<int, FIN_POOL>{});
     else if constexpr (BLDS)
         launch(std::integral_constant<int, FIN_SPLIT>{});
+    else
+        return false;
+    return true;
 }
 
 // Rows of the padded map that the windows of `cpos` consecutive positions touch, at
@@ -2466,7 +2469,7 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
     else
         hipLaunchKernelGGL(k_pad_first_spike<false>, pad_grid, dim3(256), pad_lds, st, wave, g, rows_per_chunk, nchunk, ny,
                            tpad, weight, nw, wper, wmax, wmin);
-    if (inf_mode || !blds || streamed) {  // fragments in the workspace (the finite-threshold kernel with LDS room builds its own)
+    if (inf_mode || !blds) {  // fragments in the workspace (the finite-threshold kernel with LDS room builds its own)
         if (g.CP % 32 == 0 && arith != 1) {
             hipLaunchKernelGGL(k_split_weights_cells, dim3((unsigned)(g.ntiles * (g.CP / 8))), dim3(256), 0, st, weight,
                                g, wmax, wmin, n_wmax, frag, koff2, inv_scale, wbf16);
@@ -2525,8 +2528,9 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
         }
 #undef SPK_STR
     } else {
+        bool launched = false;
 #define SPK_FIN(G, BL, AL)                                                                                          \
-    launch_fin_form<G, BL, AL>(pooled, tpad, frag, koff2, inv_scale, wbf16, weight, wmax, wmin, n_wmax, g, n_pairs,   \
+    launched = launch_fin_form<G, BL, AL>(pooled, tpad, frag, koff2, inv_scale, wbf16, weight, wmax, wmin, n_wmax, g, n_pairs,   \
                                n_chunks, cpi, chunk_tiles, band_pos, np_max, a_words, fin_lds, potentials, spikes,    \
                                t_first, v_first, pool, arith, st)
         const int sel = (vec ? 4 : 0) + (blds ? 2 : 0) + (alds ? 1 : 0);
@@ -2541,6 +2545,7 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
             default: SPK_FIN(4, true, true); break;
         }
 #undef SPK_FIN
+        SPK_REQUIRE(launched, SPK_E_RANGE, "spk_conv_fire: no kernel form for this call");
     }
     return spk::check_launch("spk_conv_fire");
 }
