@@ -2501,9 +2501,9 @@ int conv_fire(const uint8_t *wave, bool times, int B, int T, int Cin, int H, int
         // Steps a wave takes at a time: those of 3, 4 and 5 with the fewest steps computed past T,
         // of equals the most (fewer passes over the fragments).  T = 15 with 3 by two groups
         // computes 18, with 4 16: 8 images of 16 64x64 maps, 64 features of 7x7, 135 : 122 us, of
-        // 32 maps and 5x5 135 : 121; with the fragments read from L2 by every wave, 5 steps at a
-        // time, 122 and 122 (but 240 for 96 maps and 3x3, with unaligned maps 1.8 times as much as
-        // here, and 107 : 112 with 8 maps and 9x9, where a step has only 21 products).
+        // 32 maps and 5x5 135 : 121.  (With the fragments read from L2 by every wave, 3 steps at a
+        // time in the form with separate store waves, 122 and 122; 107 : 112 for 8 maps and 9x9, the
+        // fewest K-steps that are streamed, but 240 : 127 for 96 maps and 3x3.)
         auto steps_of = [&](int tg) {
             int best = 5;
             for (int tb = 4; tb >= 3; --tb)
