@@ -10,13 +10,13 @@
 // select, t_first and wave, with the intensity map never leaving LDS (it is
 // written out only when the caller asks for it).  Larger maps take many
 // workgroups per image in every step:
-//   1. k_enc_prepare analyses the bank once and clears the digit histograms;
+//   1. k_enc_prepare analyses the bank once and clears the digit histograms (for the tiles);
 //   2. k_filter_tile: same-size cross-correlation of each u8 image with the C
 //      filters (exact integer sums, or double accumulation over the non-zero
 //      taps, one rounding to float, then values below the threshold set to 0),
 //      one workgroup per (image, tile), counting the first digit of the
 //      positive intensities on the way (k_filter, one workgroup per band of
-//      rows, for banks of more than MAX_DERIV_C channels);
+//      rows, for few outputs and for banks of more than MAX_DERIV_C channels);
 //   3. k_rank_select .. k_rank_resolve: the T-1 bin boundaries, the keys
 //      (float bits of I) << 32 | ~index  at the ranks ceil((j+1) n / T), by a
 //      13-bit first digit per image and then, per digit that holds a boundary,
@@ -1496,17 +1496,18 @@ __global__ __launch_bounds__(ENC_THREADS) void k_enc_prepare(const float *__rest
 // this kernel 45 and 29 us, counting included.
 constexpr int FT_H = 32, FT_W = 64;
 __global__ __launch_bounds__(ENC_THREADS) void k_filter_tile(const uint8_t *__restrict__ img, int H, int W, int C,
-                                                             int KF, float thr, int ntx, int nty,
+                                                             int KF, float thr, int ntx, int nty, int tw, int th,
                                                              const int *__restrict__ bank, float *__restrict__ out,
                                                              uint32_t *__restrict__ hist) {
     extern __shared__ uint4 lds4[];
     __shared__ int ints[8 * MAX_DERIV_C];
     const int tid = threadIdx.x;
     const int tx = blockIdx.x % ntx, ty = (blockIdx.x / ntx) % nty, b = blockIdx.x / (ntx * nty);
-    const int x0 = tx * FT_W, y0 = ty * FT_H, p = (KF - 1) / 2;
-    const int rows = min(FT_H, H - y0), Hs = FT_H + KF - 1, Wp = small_filter_wp(FT_W, KF);
+    const int x0 = tx * tw, y0 = ty * th, p = (KF - 1) / 2;
+    const int rows = min(th, H - y0), cols = min(tw, W - x0), nxg = (cols + 7) / 8;
+    const int Hs = rows + KF - 1, Wp = small_filter_wp(cols, KF);
     uint32_t *pairs = reinterpret_cast<uint32_t *>(lds4);
-    uint32_t *h = pairs + (Hs * Wp + 3) / 4 * 4;
+    uint32_t *h = pairs + ((FT_H + KF - 1) * small_filter_wp(FT_W, KF) + 3) / 4 * 4;
     uint32_t *taps = h + (hist ? RK_BINS / 2 : 0);
     const int ncomp = bank[0], sexp = bank[1], words = bank[2];
     const uint8_t *im = img + (int64_t)b * H * W;
@@ -1533,13 +1534,13 @@ __global__ __launch_bounds__(ENC_THREADS) void k_filter_tile(const uint8_t *__re
     const int *bbox = ints, *deriv = bbox + 4 * C, *order = deriv + C, *toff = order + C, *tstr = toff + C;
     const FiltCtx fx{rows, W, C, Wp, thr, pairs, taps, bbox, deriv, toff, tstr, sexp >= 0 ? ldexp(1.0, -sexp) : 1.0,
                      nullptr, nullptr};
-    constexpr int PER = FT_H * FT_W / 8;  // items per channel
+    // items (slot, row, 8 columns); quotients by multiplication: exact, the items being fewer than 2^15
+    const uint32_t per = (uint32_t)(rows * nxg), mper = 0xFFFFFFFFu / per + 1, mnx = 0xFFFFFFFFu / nxg + 1;
     const bool al16 = (W & 3) == 0 && ((uintptr_t)out & 15) == 0;
-    for (int it = tid; it < ncomp * PER; it += ENC_THREADS) {
-        const int slot = it / PER, rem = it - slot * PER;
-        const int y = (rem >> 6) * 8 + ((rem >> 3) & 7), xg = rem & 7;
-        const int nx = min(8, W - x0 - 8 * xg);
-        if (y >= rows || nx <= 0) continue;
+    for (int it = tid; it < ncomp * (int)per; it += ENC_THREADS) {
+        const int slot = per == 1 ? it : (int)__umulhi((uint32_t)it, mper), rem = it - slot * (int)per;
+        const int y = nxg == 1 ? rem : (int)__umulhi((uint32_t)rem, mnx), xg = rem - y * nxg;
+        const int nx = min(8, cols - 8 * xg);
         const int c = order[slot];
         double val[8];
         if (sexp >= 0)
@@ -1789,9 +1790,17 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
     SPK_REQUIRE(filter_lds(R) <= 65536, SPK_E_RANGE, "spk_encode_latency: %d filters of %dx%d on width %d do not fit",
                 C, KF, KF, W);
     bool counted = false;
-    const int ntx = (W + FT_W - 1) / FT_W, nty = (H + FT_H - 1) / FT_H;
-    // (a launch has fewer than 2^32 threads: very many narrow images take bands, which are fewer)
-    if (C <= MAX_DERIV_C && (int64_t)B * ntx * nty < (1LL << 24)) {
+    // tiles, evened out over the image's sides
+    const int th = (int)spk::ceil_div(H, spk::ceil_div(H, FT_H)), nty = (H + th - 1) / th;
+    const int tw = (int)spk::align_up((size_t)spk::ceil_div(W, spk::ceil_div(W, FT_W)), 8), ntx = (W + tw - 1) / tw;
+    // Few outputs are made sooner by bands cut thin than by tiles after an analysis of the bank,
+    // which takes 5 us by itself.  Measured (bands : tiles, us; 4 Gabor filters of 5x5, 6 DoG
+    // filters up to 13x13, 6 random ones of 13x13): one 28x28 image 4.6 : 10.3, 12 : 15, 10 : 38;
+    // one of 160x250 5.9 : 16, 18 : 20, 23 : 70; 300 of 16x16 5.4 : 9.7, 14 : 15, 20 : 26; 4 of
+    // 160x250 13 : 16, 39 : 21, 57 : 71; 200 of 28x28 11 : 11, 26 : 17, 39 : 42; 1000 of 28x28
+    // 18 : 17, 49 : 24, 84 : 79.  (A launch has fewer than 2^32 threads: very many narrow images
+    // take bands, which are fewer.)
+    if (C <= MAX_DERIV_C && B * p.N > (1 << 19) && (int64_t)B * ntx * nty < (1LL << 24)) {
         // the digits are counted while they are made when 16-bit counters hold a tile's entries
         const bool rank = (t_first || wave) && p.N > SMALL_MAX && T > 1;
         counted = rank && C * FT_H * FT_W < 65536;
@@ -1803,7 +1812,7 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
         const size_t lds = up16((size_t)(FT_H + KF - 1) * small_filter_wp(FT_W, KF) * sizeof(uint32_t)) +
                            (counted ? RK_BINS / 2 * sizeof(uint32_t) : 0) + std::max(taps_lds, itaps_lds);
         hipLaunchKernelGGL(k_filter_tile, dim3((unsigned)((int64_t)B * ntx * nty)), dim3(ENC_THREADS), lds, st, image,
-                           H, W, C, KF, filter_threshold, ntx, nty, bank, I, counted ? rw.hist : nullptr);
+                           H, W, C, KF, filter_threshold, ntx, nty, tw, th, bank, I, counted ? rw.hist : nullptr);
     } else {
         int nb = (H + R - 1) / R;
         // few images (online steps): more, thinner bands, so that more workgroups share them

@@ -822,7 +822,8 @@ def test_encode_parity(case):
 
 @pytest.mark.parametrize("B,H,W", [(2, 160, 250), (2, 156, 286), (3, 100, 120)])
 def test_encode_few_images_stay_in_their_buffers(B, H, W):
-    # few images by tiles: the last ones of a side are cut short, and none lies past the batch
+    # few images: the filter's bands are cut thinner than LDS asks for, and a height that they
+    # do not divide must not leave workgroups for images past the batch
     g = synth.rng(460, H)
     img, bank = synth.pink_noise_images(g, B, H, W), synth.gabor_bank()
     room = torch.full((3 * B, 4, H, W), -7.0, dtype=torch.float32, device="cuda")
@@ -849,6 +850,30 @@ def test_encode_few_images_by_bands_stay_in_their_buffers(B, C, H, W):
     assert_equal(host(inten), I, "intensities")
     assert_equal(host(tf), rtf, "t_first")
     assert (host(room[B:]) == -7.0).all(), "intensities past the batch were written"
+
+
+# Filter by tiles (more than 2^19 outputs): sides of one tile and a little more, which are evened out
+# (33 rows: 17 and 16; 65 columns: 40 and 25), of less than a group of 8 columns, whole tiles; both
+# arithmetic forms; channels that negate the one before; more channels than tiles count digits for
+@pytest.mark.parametrize("kind", ["dog", "integer", "double"])
+@pytest.mark.parametrize("B,H,W", [(60, 33, 65), (31, 64, 64), (170, 400, 3), (900, 28, 28), (5, 161, 253)])
+def test_encode_tiles_parity(kind, B, H, W):
+    g = synth.rng(464, H + len(kind))
+    n = 3 if B > 3 else B  # distinct images, repeated
+    img = g.integers(0, 256, (n, H, W)).astype(np.uint8)
+    bank = {"dog": synth.dog_bank, "integer": lambda: (g.integers(-64, 65, (5, 7, 7)) / 64.0).astype(np.float32),
+            "double": lambda: g.normal(0, 1, (40 if B == 900 else 7, 5, 5)).astype(np.float32)}[kind]()
+    assert B * len(bank) * H * W > 1 << 19
+    wave, tf, inten = spk.spk_encode_latency(dev(img[np.arange(B) % n]), dev(bank), 7, 0.5, intensities=None)
+    _, _, lone = spk.spk_encode_latency(dev(img[np.arange(B) % n]), dev(bank), 7, 0.5, wave=False, t_first=False,
+                                        intensities=None)
+    sync()
+    I, rtf, rwave = orc.encode(img, bank, 7, 0.5)
+    pick = torch.arange(B, device="cuda") % n
+    assert torch.equal(lone, dev(I)[pick]), "intensities alone"
+    assert torch.equal(inten, dev(I)[pick]), "intensities"
+    assert torch.equal(tf, dev(rtf)[pick]), "t_first"
+    assert torch.equal(wave, dev(rwave)[pick]), "wave"
 
 
 def test_encode_more_tiles_than_a_launch_has_workgroups():
