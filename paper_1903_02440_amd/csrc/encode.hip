@@ -829,13 +829,14 @@ __device__ __forceinline__ void filter_sums(const FiltCtx &fx, int k, int c, int
 #pragma unroll
         for (int j = 0; j < CW; ++j) val[j] = (double)acc[j] * fx.scale;
     } else {
+        double acc[CW];  // (its own: with the caller's array every branch of the switch copies the sums)
 #pragma unroll
-        for (int j = 0; j < CW; ++j) val[j] = 0.0;
+        for (int j = 0; j < CW; ++j) acc[j] = 0.0;
         const double *fc = reinterpret_cast<const double *>(fx.taps) + fx.toff[k];
         const int ts = fx.tstr[k];
         for (int ky = ya; ky <= yb; ++ky) {
             const uint32_t *row = fx.pairs + (y + ky) * fx.Wp + CW * xg + xa;
-            tap_row(row, fc + (ky - ya) * ts, wx, val,
+            tap_row(row, fc + (ky - ya) * ts, wx, acc,
                     [](const uint32_t *r, const double *t, double(&a)[8]) { filter_taps<8>(r, t, a); },
                     [](int n, const uint32_t *r, const double *t, double(&a)[8]) {
                         switch (n) {
@@ -850,6 +851,8 @@ __device__ __forceinline__ void filter_sums(const FiltCtx &fx, int k, int c, int
                         }
                     });
         }
+#pragma unroll
+        for (int j = 0; j < CW; ++j) val[j] = acc[j];
     }
 }
 
