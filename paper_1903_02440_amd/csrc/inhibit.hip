@@ -387,10 +387,10 @@ __global__ __launch_bounds__(256) void k_pool_potentials_2x2_even(const float *_
 // 256 28 : 37.  With wave and potentials 64 maps of 14x14, 1000 images 507 : 363; 8 of
 // 64x64, 16 images 36 : 24, 128 109 : 163; 12 of 7x7, 1000 images 20 : 28; 4 of 9x9, 100
 // images 7.5 : 8.7; 10 of 1x1, 1000 images 42 : 10, 100,000 147 : 818.
-bool pw_each(int64_t B, int C, int64_t HW, int64_t nrun, bool vec, bool steps) {
+bool pw_each(int64_t B, int64_t C, int64_t HW, int64_t nrun, bool vec, bool steps) {
     const int64_t loc = B * HW;
-    if (steps) return C < 8 || loc > (vec ? 262144 : 40000) || B * nrun > std::max(4096, 64 * C);
-    return C < (vec ? 32 : 100) || HW > 448 || loc > (vec ? std::max(12800, 200 * C) : 50 * C) || B > 2048;
+    if (steps) return C < 8 || loc > (vec ? 262144 : 40000) || B * nrun > std::max<int64_t>(4096, 64 * C);
+    return C < (vec ? 32 : 100) || HW > 448 || loc > (vec ? std::max<int64_t>(12800, 200 * C) : 50 * C) || B > 2048;
 }
 
 }  // namespace
