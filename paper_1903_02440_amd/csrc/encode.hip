@@ -1499,15 +1499,15 @@ __global__ __launch_bounds__(ENC_THREADS) void k_enc_prepare(const float *__rest
 // this kernel 45 and 29 us, counting included.
 constexpr int FT_H = 32, FT_W = 64;
 __global__ __launch_bounds__(ENC_THREADS) void k_filter_tile(const uint8_t *__restrict__ img, int H, int W, int C,
-                                                             int KF, float thr, int ntx, int nty, int tw, int th,
+                                                             int KF, float thr, int ntx, int nty, int th,
                                                              const int *__restrict__ bank, float *__restrict__ out,
                                                              uint32_t *__restrict__ hist) {
     extern __shared__ uint4 lds4[];
     __shared__ int ints[8 * MAX_DERIV_C];
     const int tid = threadIdx.x;
     const int tx = blockIdx.x % ntx, ty = (blockIdx.x / ntx) % nty, b = blockIdx.x / (ntx * nty);
-    const int x0 = tx * tw, y0 = ty * th, p = (KF - 1) / 2;
-    const int rows = min(th, H - y0), cols = min(tw, W - x0), nxg = (cols + 7) / 8;
+    const int x0 = tx * FT_W, y0 = ty * th, p = (KF - 1) / 2;
+    const int rows = min(th, H - y0), cols = min(FT_W, W - x0), nxg = (cols + 7) / 8;
     const int Hs = rows + KF - 1, Wp = small_filter_wp(cols, KF);
     uint32_t *pairs = reinterpret_cast<uint32_t *>(lds4);
     uint32_t *h = pairs + ((FT_H + KF - 1) * small_filter_wp(FT_W, KF) + 3) / 4 * 4;
@@ -1538,7 +1538,14 @@ __global__ __launch_bounds__(ENC_THREADS) void k_filter_tile(const uint8_t *__re
     const FiltCtx fx{rows, W, C, Wp, thr, pairs, taps, bbox, deriv, toff, tstr, sexp >= 0 ? ldexp(1.0, -sexp) : 1.0,
                      nullptr, nullptr};
     // items (slot, row, 8 columns); quotients by multiplication: exact, the items being fewer than 2^15
-    const uint32_t per = (uint32_t)(rows * nxg), mper = 0xFFFFFFFFu / per + 1, mnx = 0xFFFFFFFFu / nxg + 1;
+    // (whole tiles' known: the divisions take 0.5 us of a tile)
+    const bool whole = rows == FT_H && nxg == FT_W / 8;  // uniform
+    const uint32_t per = (uint32_t)(rows * nxg);
+    uint32_t mper = 0x100000000ull / (FT_H * FT_W / 8), mnx = 0x100000000ull / (FT_W / 8);
+    if (!whole) {
+        mper = 0xFFFFFFFFu / per + 1;
+        mnx = 0xFFFFFFFFu / (uint32_t)nxg + 1;
+    }
     const bool al16 = (W & 3) == 0 && ((uintptr_t)out & 15) == 0;
     for (int it = tid; it < ncomp * (int)per; it += ENC_THREADS) {
         const int slot = per == 1 ? it : (int)__umulhi((uint32_t)it, mper), rem = it - slot * (int)per;
@@ -1793,9 +1800,10 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
     SPK_REQUIRE(filter_lds(R) <= 65536, SPK_E_RANGE, "spk_encode_latency: %d filters of %dx%d on width %d do not fit",
                 C, KF, KF, W);
     bool counted = false;
-    // tiles, evened out over the image's sides
-    const int th = (int)spk::ceil_div(H, spk::ceil_div(H, FT_H)), nty = (H + th - 1) / th;
-    const int tw = (int)spk::align_up((size_t)spk::ceil_div(W, spk::ceil_div(W, FT_W)), 8), ntx = (W + tw - 1) / tw;
+    // up to four tiles evened out over the height (500 images of 36x36, 6 filters of 13x13: 105 ->
+    // 72 us); of more, whole ones and the rest, as across
+    const int th = H > 4 * FT_H ? FT_H : (int)spk::ceil_div(H, spk::ceil_div(H, FT_H)), nty = (H + th - 1) / th;
+    const int ntx = (W + FT_W - 1) / FT_W;
     // Few outputs are made sooner by bands cut thin than by tiles after an analysis of the bank,
     // which takes 5 us by itself.  Measured (bands : tiles, us; 4 Gabor filters of 5x5, 6 DoG
     // filters up to 13x13, 6 random ones of 13x13): one 28x28 image 4.6 : 10.3, 12 : 15, 10 : 38;
@@ -1815,7 +1823,7 @@ extern "C" int spk_encode_latency(const uint8_t *image, int B, int H, int W, con
         const size_t lds = up16((size_t)(FT_H + KF - 1) * small_filter_wp(FT_W, KF) * sizeof(uint32_t)) +
                            (counted ? RK_BINS / 2 * sizeof(uint32_t) : 0) + std::max(taps_lds, itaps_lds);
         hipLaunchKernelGGL(k_filter_tile, dim3((unsigned)((int64_t)B * ntx * nty)), dim3(ENC_THREADS), lds, st, image,
-                           H, W, C, KF, filter_threshold, ntx, nty, tw, th, bank, I, counted ? rw.hist : nullptr);
+                           H, W, C, KF, filter_threshold, ntx, nty, th, bank, I, counted ? rw.hist : nullptr);
     } else {
         int nb = (H + R - 1) / R;
         // few images (online steps): more, thinner bands, so that more workgroups share them

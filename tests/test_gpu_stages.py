@@ -852,8 +852,8 @@ def test_encode_few_images_by_bands_stay_in_their_buffers(B, C, H, W):
     assert (host(room[B:]) == -7.0).all(), "intensities past the batch were written"
 
 
-# Filter by tiles (more than 2^19 outputs): sides of one tile and a little more, which are evened out
-# (33 rows: 17 and 16; 65 columns: 40 and 25), of less than a group of 8 columns, whole tiles; both
+# Filter by tiles (more than 2^19 outputs): sides of one tile and a little more (33 rows, evened out:
+# 17 and 16; 65 columns: 64 and 1), of less than a group of 8 columns, whole tiles; both
 # arithmetic forms; channels that negate the one before; more channels than tiles count digits for
 @pytest.mark.parametrize("kind", ["dog", "integer", "double"])
 @pytest.mark.parametrize("B,H,W", [(60, 33, 65), (31, 64, 64), (170, 400, 3), (900, 28, 28), (5, 161, 253)])
